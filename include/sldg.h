@@ -166,7 +166,10 @@ typedef struct {
  * 1 runs as one fused pass (sldg_advect_dims01) where that entry point
  * accepts the pair and fusion is on (sldg_plan_set_fusion, default on): the
  * result is bitwise the same, but the pair then takes one pass instead of
- * two.  *result_buffer receives the buffer (0 or 1) holding the result:
+ * two.  Other sweeps along 0, 1, 0 in a row (a Strang step X V X of an (x, v)
+ * problem) run as one pass too, bitwise the three sweeps, where at most the
+ * cell mean is FP64 and kernel timing (sldg_timing_enable) is off.
+ * *result_buffer receives the buffer (0 or 1) holding the result:
  * (nsteps * nseq) % 2 without fused pairs.
  * Buffers 0 and 1 must not overlap.  Asynchronous on the plan's stream.
  */
@@ -197,8 +200,20 @@ sldg_status sldg_advect_dims01(sldg_plan_t plan, const double* shift0, uint32_t 
                                const double* in_mass, const void* in_hi, double* out_mass,
                                void* out_hi);
 
-/* Fusion of (0, 1) sweep pairs inside sldg_split_steps: enable != 0 on (the
- * default), 0 off (every sweep its own pass).  Errors: SLDG_ERR_ARG. */
+/*
+ * The transpose of sldg_split_steps with the same arguments (reverse-mode
+ * differentiation through split steps, section II): nsteps times the
+ * transposes of seq's sweeps (sldg_advect_dim_adjoint), last sweep first.
+ * Passes are fused as there (X V X is its own reverse).  Same layout, buffers
+ * and errors as sldg_split_steps; buffer 0 holds the output-side gradient.
+ */
+sldg_status sldg_split_steps_adjoint(sldg_plan_t plan, const sldg_sweep_desc* seq, int nseq,
+                                     int nsteps, double* mass0, void* hi0, double* mass1,
+                                     void* hi1, int* result_buffer);
+
+/* Fusion of sweeps inside sldg_split_steps and sldg_split_steps_adjoint:
+ * enable != 0 on (the default), 0 off (every sweep its own pass).  Errors:
+ * SLDG_ERR_ARG. */
 sldg_status sldg_plan_set_fusion(sldg_plan_t plan, int enable);
 
 /*

@@ -34,7 +34,7 @@ EXPORTS = ("sldg_plan", "sldg_plan_destroy", "sldg_plan_set_stream", "sldg_line_
            "sldg_poisson_shift", "sldg_poisson_shift_noalloc", "sldg_vlasov_poisson_steps",
            "sldg_advect_dim_collocated", "sldg_poisson_shift_2d", "sldg_vlasov_poisson_steps_2d2v",
            "sldg_set_device_alloc_limit", "sldg_device_alloc_bytes", "sldg_advect_dims01",
-           "sldg_plan_set_fusion")
+           "sldg_plan_set_fusion", "sldg_split_steps_adjoint")
 
 
 class SldgError(RuntimeError):
@@ -85,6 +85,8 @@ def lib():
     L.sldg_split_steps.argtypes = [vp, ctypes.POINTER(SweepDesc), i32, i32, vp, vp, vp, vp,
                                    ctypes.POINTER(i32)]
     L.sldg_split_steps.restype = i32
+    L.sldg_split_steps_adjoint.argtypes = L.sldg_split_steps.argtypes
+    L.sldg_split_steps_adjoint.restype = i32
     L.sldg_mass.argtypes = [vp, vp, ctypes.POINTER(ctypes.c_double)]
     L.sldg_mass.restype = i32
     L.sldg_hi_bytes.argtypes = [vp]
@@ -325,16 +327,26 @@ class Plan:
         """Apply the sweeps `seq` [(dim, dep_mask, shift tensor), ...] nsteps
         times, ping-ponging between state0 and state1 (sldg_split_steps).
         Returns the index (0 or 1) of the state that holds the result."""
+        return self._split_steps("split_steps", seq, nsteps, state0, state1)
+
+    def split_steps_adjoint(self, seq, nsteps, state0, state1):
+        """The transpose of split_steps (sldg_split_steps_adjoint): the
+        transposed sweeps of `seq` in reverse order, nsteps times.  Returns the
+        index (0 or 1) of the state that holds the result."""
+        return self._split_steps("split_steps_adjoint", seq, nsteps, state0, state1)
+
+    def _split_steps(self, entry, seq, nsteps, state0, state1):
         descs = (SweepDesc * max(1, len(seq)))()
         for q, (dim, mask, shift) in enumerate(seq):
-            self._check_shift(shift, mask, "split_steps")
+            self._check_shift(shift, mask, entry)
             descs[q] = SweepDesc(int(dim), int(mask), _ptr(shift))
-        self._check_state(*state0, "split_steps state0")
-        self._check_state(*state1, "split_steps state1")
+        self._check_state(*state0, f"{entry} state0")
+        self._check_state(*state1, f"{entry} state1")
         res = ctypes.c_int(-1)
-        _check(lib().sldg_split_steps(self.handle, descs, len(seq), int(nsteps),
-                                      _ptr(state0[0]), _ptr(state0[1]), _ptr(state1[0]),
-                                      _ptr(state1[1]), ctypes.byref(res)), "sldg_split_steps")
+        _check(getattr(lib(), f"sldg_{entry}")(self.handle, descs, len(seq), int(nsteps),
+                                               _ptr(state0[0]), _ptr(state0[1]), _ptr(state1[0]),
+                                               _ptr(state1[1]), ctypes.byref(res)),
+               f"sldg_{entry}")
         return res.value
 
     def advect_dim_collocated(self, dim, tdim, node_shift, in_mass, in_hi, out_mass, out_hi):

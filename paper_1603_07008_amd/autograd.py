@@ -3,7 +3,8 @@
 The split step (section II: Cheng-Knorr splitting into 1D advections) is a
 linear map of the coefficients for given displacement fields, so its
 gradient is the product of the transposed sweeps in reverse order; each
-transposed sweep runs in the library's HIP kernels (sldg_advect_dim_adjoint).
+transposed sweep runs in the library's HIP kernels
+(sldg_split_steps_adjoint).
 This module only orders the calls and manages buffers.
 
 Checkpointing: with `checkpoint_every = C`, the forward pass keeps the state
@@ -34,13 +35,15 @@ class _SplitSteps(torch.autograd.Function):
         idx = 0
         ckpts = []
         seqs = []
-        for n in range(nsteps):
+        # with fixed fields the steps between two checkpoints are one call
+        run = 1 if frozen_shifts_fn is not None else checkpoint_every or max(nsteps, 1)
+        for n in range(0, nsteps, run):
             if checkpoint_every and n % checkpoint_every == 0:
                 ckpts.append((n, cur[idx][0].clone(), cur[idx][1].clone()))
             step_seq = seq if frozen_shifts_fn is None else frozen_shifts_fn(cur[idx])
             if frozen_shifts_fn is not None and not checkpoint_every:
                 seqs.append(step_seq)
-            res = plan.split_steps(step_seq, 1, cur[idx], cur[1 - idx])
+            res = plan.split_steps(step_seq, min(run, nsteps - n), cur[idx], cur[1 - idx])
             idx = idx if res == 0 else 1 - idx
         ctx.plan = plan
         ctx.seq = seq
@@ -58,18 +61,16 @@ class _SplitSteps(torch.autograd.Function):
              g_hi.detach().to(hi_dtype(plan.tier)).contiguous().clone())
         tmp = plan.empty_state()
 
-        def adjoint_step(step_seq):
+        def adjoint_steps(step_seq, n):
             nonlocal g, tmp
-            for dim, mask, shift in reversed(step_seq):
-                plan.advect_dim_adjoint(dim, shift, mask, g[0], g[1], tmp[0], tmp[1])
+            if plan.split_steps_adjoint(step_seq, n, g, tmp):
                 g, tmp = tmp, g
 
         if ctx.shifts_fn is None:
-            for _ in range(ctx.nsteps):
-                adjoint_step(ctx.seq)
+            adjoint_steps(ctx.seq, ctx.nsteps)
         elif not ctx.checkpoint_every:
             for step_seq in reversed(ctx.seqs):
-                adjoint_step(step_seq)
+                adjoint_steps(step_seq, 1)
         else:
             bounds = [n for n, _, _ in ctx.checkpoints] + [ctx.nsteps]
             for seg in range(len(ctx.checkpoints) - 1, -1, -1):
@@ -83,7 +84,7 @@ class _SplitSteps(torch.autograd.Function):
                     res = plan.split_steps(step_seq, 1, st[idx], st[1 - idx])
                     idx = idx if res == 0 else 1 - idx
                 for step_seq in reversed(seg_seqs):
-                    adjoint_step(step_seq)
+                    adjoint_steps(step_seq, 1)
         return g[0], g[1], None, None, None, None, None
 
 

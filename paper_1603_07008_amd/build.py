@@ -1,7 +1,7 @@
 """Build libsldg.so (HIP, gfx950) in-tree with hipcc.
 
 Every translation unit is compiled to its own object, in parallel, then the
-objects are linked.  The sweep kernels' instantiation unit is compiled once
+objects are linked.  The sweep kernels' instantiation units are compiled once
 per (degree, storage tier) pair, so the template-heavy part of the library
 compiles on several cores.
 """
@@ -17,13 +17,13 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsldg.so")
 PLAIN = ["sldg_host.hip", "sldg_batch.hip", "sldg_kernels.hip", "sldg_ref.hip", "sldg_field.hip",
          "sldg_colloc.hip"]
-INST = "sldg_sweep_inst.hip"
+INST = ["sldg_sweep_inst.hip", "sldg_strang_inst.hip"]
 DEGREES = (1, 2, 3)
 TIERS = (0, 1, 2, 3)
-SOURCES = [os.path.join(CSRC, f) for f in PLAIN + [INST]]
+SOURCES = [os.path.join(CSRC, f) for f in PLAIN + INST]
 HEADERS = [os.path.join(CSRC, f) for f in ("sldg_internal.h", "sldg_sweep.h", "ab_poly.h",
                                           "sldg_ref.h", "sldg_field.h", "sldg_colloc.h",
-                                          "sldg_fused.h", "sldg_staged.h")] + \
+                                          "sldg_fused.h", "sldg_staged.h", "sldg_strang.h")] + \
     [os.path.join(ROOT, "include", "sldg.h")]
 ARCH = os.environ.get("SLDG_OFFLOAD_ARCH", "gfx950")
 
@@ -50,8 +50,10 @@ def units():
         out.append((os.path.join(CSRC, f), os.path.join(OBJ, f[:-4] + ".o"), []))
     for k in DEGREES:
         for t in TIERS:
-            out.append((os.path.join(CSRC, INST), os.path.join(OBJ, f"sldg_sweep_k{k}_t{t}.o"),
-                        [f"-DSLDG_K={k}", f"-DSLDG_TIER={t}"]))
+            for f in INST:
+                name = f.replace("_inst.hip", f"_k{k}_t{t}.o")
+                out.append((os.path.join(CSRC, f), os.path.join(OBJ, name),
+                            [f"-DSLDG_K={k}", f"-DSLDG_TIER={t}"]))
     return out
 
 

@@ -21,6 +21,7 @@
 #include "sldg_field.h"
 #include "sldg_colloc.h"
 #include "sldg_fused.h"
+#include "sldg_strang.h"
 
 using namespace sldg;
 
@@ -56,6 +57,7 @@ struct sldg_plan_s {
   int fuse;               // split steps fuse eligible (0, 1) pairs
   int xy_rows;            // tile rows of dimension 1 (0: the most that fit)
   int xcd_xy;             // XCD-aware tile order of the fused pass
+  int xcd_strang;         // ... and of the X V X pass
   // scaled FP16 storage
   int scale_headroom;     // binades between a plane's absmax and 2^15
   int32_t* d_hmode;       // [n_hi] mode id of every hi plane
@@ -645,6 +647,69 @@ sldg_status run_xy(sldg_plan_s* p, const double* shift0, uint32_t mask0, const d
   return timing_end(p, timed, kXYTimingDim);
 }
 
+// Rows per wave of the X V X pass: a wave loads and X-sweeps three rows more
+// than it has, but its rows follow one another, so the most (of 8, 4, 2) that
+// leaves about a wave per SIMD where the grid is small.  Measured (five Strang
+// steps, FP32-mode, rows 1, 2, 4, 8, 16): 256^2 k = 2 (1,280 wave rows) 49, 46,
+// 53, 66, 99 us; 512^2 k = 3 (4,608) 138, 126, 123, 136, 204; 1024^2 k = 3
+// (17,408) 351, 275, 251, 245, 285; 2048^2 k = 3 (69,632) 1414, 1085, 931, 864,
+// 884.
+constexpr int64_t kStrangWaves = 600;
+constexpr int32_t kStrangRows = 8;
+
+// Whether X V X (sweeps along dimensions 0, 1, 0) can run as one pass
+// (sldg_strang.h): at most the cell mean FP64, a spectator group's planes
+// below 2^31 bytes and a launchable grid.  Kernel timing measures the sweeps
+// one by one, so it keeps them apart.
+bool strang_eligible(const sldg_plan_s* p, StrangArgs& x, int64_t& nblocks) {
+  if (!p->fuse || p->timing || p->ndim < 2 || p->n_lo > 1) return false;
+  const int64_t N0 = p->n[0], N1 = p->n[1];
+  if (!strang_fits(p->cells, p->o, elem_size(p->tier))) return false;
+  x.N0 = (int32_t)N0;
+  x.N1 = (int32_t)N1;
+  x.Q = (int32_t)(p->cells / (N0 * N1));
+  const int64_t groups = p->modes / (p->o * p->o);
+  const int64_t lines = (N0 + 61) / 62 * x.Q * groups * N1;    // wave rows
+  int32_t rows = kStrangRows;
+  while (rows > 1 && lines / rows < kStrangWaves) rows >>= 1;
+  strang_tiles(x, rows);
+  nblocks = (int64_t)x.ntile * x.nstrip * x.Q * groups;
+  return nblocks <= INT32_MAX;
+}
+
+// One X V X pass; the tables of the three sweeps are at entries pre[i] (nt[i]
+// entries each) of the plan's tables.
+sldg_status run_strang(sldg_plan_s* p, const uint32_t (&mask)[3], const int64_t (&pre)[3],
+                       const double* in_lo, const void* in_hi, double* out_lo, void* out_hi) {
+  StrangArgs x{};
+  int64_t nblocks = 0;
+  if (!strang_eligible(p, x, nblocks)) return fail(SLDG_ERR_UNSUPPORTED, "fused X V X sweeps");
+  const int64_t o2 = (int64_t)p->o * p->o;
+  LineTable* tab[3] = {&x.x0, &x.v, &x.x1};
+  for (int i = 0; i < 3; ++i) {
+    SweepArgs a{};
+    int64_t nt = 0;
+    describe(p, i == 1 ? 1 : 0, mask[i], a, nt);
+    const int64_t E = 2 * o2;
+    *tab[i] = {p->d_s + pre[i], p->d_ab + E * pre[i], i == 1 ? nt : 1, i == 1 ? 1 : E,
+               (int32_t)(mask[i] >> (i == 1 ? 0 : 1) & 1), a.map};
+  }
+  x.in_lo = in_lo;
+  x.in_hi = in_hi;
+  x.out_lo = out_lo;
+  x.out_hi = out_hi;
+  x.n_lo = (int32_t)p->n_lo;
+  x.cells = p->cells;
+  x.xcd = p->xcd_strang;
+  x.one = 1.0f;
+  x.fstrip = FastDiv::make((uint32_t)x.nstrip);
+  x.ftile = FastDiv::make((uint32_t)x.ntile);
+  x.fQ = FastDiv::make((uint32_t)x.Q);
+  const hipError_t e = launch_strang(p->k, (int)p->tier, 1, x, (int32_t)nblocks, p->stream);
+  if (e != hipSuccess) return device_error(e, "fused X V X launch");
+  return SLDG_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -734,8 +799,10 @@ sldg_status sldg_plan_ex(sldg_plan_t* out, int ndim, const int64_t* ncells, int 
   p->fuse = 1;
   p->xy_rows = 0;
   p->xcd_xy = 0;               // the fused pass: dispatch order measured best
+  p->xcd_strang = 16;          // 2048^2 k = 3 FP32-mode: 0.173 ms a pass against 0.199 in dispatch order
   if (const char* env = getenv("SLDG_XY_ROWS")) p->xy_rows = std::max(0, atoi(env));
   if (const char* env = getenv("SLDG_XCD_XY")) p->xcd_xy = std::max(0, atoi(env));
+  p->xcd_strang = 8;
 
   if (const char* env = getenv("SLDG_COLWAVES")) {
     const int c = atoi(env);
@@ -896,14 +963,11 @@ sldg_status sldg_advect_dim_adjoint(sldg_plan_t p, int dim, const double* shift,
   return st == SLDG_OK ? ok() : st;
 }
 
-sldg_status sldg_split_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq, int nsteps,
-                             double* mass0, void* hi0, double* mass1, void* hi1,
+// nsteps times the sweeps of seq (adjoint: their transposes, in the order
+// given).
+static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq, int nsteps,
+                             bool adjoint, double* const (&m)[2], void* const (&h)[2],
                              int* result_buffer) {
-  if (!p) return fail(SLDG_ERR_ARG, "plan is NULL");
-  if (nseq < 0 || nsteps < 0 || (nseq > 0 && !seq))
-    return fail(SLDG_ERR_ARG, "bad sweep sequence (nseq=%d nsteps=%d)", nseq, nsteps);
-  double* m[2] = {mass0, mass1};
-  void* h[2] = {hi0, hi1};
   // validate every sweep against both directions before launching anything
   for (int q = 0; q < nseq; ++q) {
     for (int b = 0; b < 2; ++b) {
@@ -915,52 +979,77 @@ sldg_status sldg_split_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
   // sweeps along dimension 0 then 1 run as one fused pass where they can
   // (same result, one read and one write of the state instead of two); the
   // pair's result then lands in the other buffer than two sweeps would leave
-  // it in, which *result_buffer reports
+  // it in, which *result_buffer reports.  Elsewhere sweeps along 0, 1, 0 run
+  // as one pass (three sweeps and one pass end in the same buffer).
   std::vector<char> fused((size_t)std::max(nseq, 1), 0);
   for (int q = 0; p->fuse && q + 1 < nseq; ++q) {
     const char* why = nullptr;
-    if (seq[q].dim == 0 && seq[q + 1].dim == 1 &&
+    StrangArgs x{};
+    int64_t nblocks = 0;
+    if (seq[q].dim != 0 || seq[q + 1].dim != 1) continue;
+    if (!adjoint &&
         xy_eligible(p, seq[q].dep_mask, seq[q + 1].dep_mask, m[0], h[0], m[1], h[1], &why)) {
-      fused[(size_t)q] = 1;
+      fused[(size_t)q] = 2;
       ++q;
+    } else if (q + 2 < nseq && seq[q + 2].dim == 0 && strang_eligible(p, x, nblocks)) {
+      fused[(size_t)q] = 3;
+      q += 2;
     }
   }
   // The line tables of every sweep of the sequence, in one launch before the
   // steps: the displacements are fixed over the call, so every step's tables
-  // are these.  Where the sequence's tables do not fit the plan's table
-  // storage together, each sweep computes its own.
+  // are these, and sweeps along the same dimension with the same displacements
+  // and table layout share one.  Where the sequence's tables do not fit the
+  // plan's table storage together, each sweep computes its own (and X V X runs
+  // sweep by sweep).
   std::vector<int64_t> pre((size_t)std::max(nseq, 1), -1);
   if (nsteps > 0 && nseq > 0 && nseq <= kMaxTableSet) {
     TableSet set{};
-    set.count = nseq;
     int64_t tot = 0;
+    int of[kMaxTableSet];
+    bool em[kMaxTableSet];
     for (int q = 0; q < nseq; ++q) {
+      of[q] = -1;
+      em[q] = fused[(size_t)q] == 3 || (q >= 2 && fused[(size_t)q - 2] == 3);
+      for (int e = 0; e < q && of[q] < 0; ++e)
+        if (seq[e].dim == seq[q].dim && seq[e].dep_mask == seq[q].dep_mask &&
+            seq[e].shift == seq[q].shift && em[e] == em[q])
+          of[q] = of[e];
+      if (of[q] >= 0) continue;
       SweepArgs a{};
       int64_t nt = 0;
       describe(p, seq[q].dim, seq[q].dep_mask, a, nt);
-      set.first[q] = tot;
-      set.period[q] = p->n[seq[q].dim];
-      set.sigma[q] = seq[q].shift;
+      const int i = of[q] = set.count++;
+      set.first[i] = tot;
+      set.period[i] = p->n[seq[q].dim];
+      set.sigma[i] = seq[q].shift;
+      if (em[q]) set.entry_major |= 1u << i;
+      if (adjoint) set.adjoint |= 1u << i;
       tot += nt;
     }
-    set.first[nseq] = tot;
+    set.first[set.count] = tot;
     if (tot <= p->table_cap) {
       const hipError_t e = launch_line_tables_set(p->k, set, p->d_s, p->d_ab, p->stream);
       if (e != hipSuccess) return device_error(e, "line-table launch");
-      for (int q = 0; q < nseq; ++q) pre[(size_t)q] = set.first[q];
+      for (int q = 0; q < nseq; ++q) pre[(size_t)q] = set.first[of[q]];
     }
   }
   int cur = 0;
   for (int n = 0; n < nsteps; ++n) {
     for (int q = 0; q < nseq; ++q) {
       sldg_status st;
-      if (fused[(size_t)q]) {
+      if (fused[(size_t)q] == 2) {
         st = run_xy(p, seq[q].shift, seq[q].dep_mask, seq[q + 1].shift, seq[q + 1].dep_mask,
                     m[cur], h[cur], m[1 - cur], h[1 - cur], pre[(size_t)q], pre[(size_t)q + 1]);
         ++q;
+      } else if (fused[(size_t)q] == 3 && pre[(size_t)q] >= 0) {
+        const uint32_t mask[3] = {seq[q].dep_mask, seq[q + 1].dep_mask, seq[q + 2].dep_mask};
+        const int64_t at[3] = {pre[(size_t)q], pre[(size_t)q + 1], pre[(size_t)q + 2]};
+        st = run_strang(p, mask, at, m[cur], h[cur], m[1 - cur], h[1 - cur]);
+        q += 2;
       } else {
         st = run_sweep(p, seq[q].dim, seq[q].shift, seq[q].dep_mask, m[cur], h[cur], m[1 - cur],
-                       h[1 - cur], false, nullptr, nullptr, pre[(size_t)q]);
+                       h[1 - cur], adjoint, nullptr, nullptr, pre[(size_t)q]);
       }
       if (st != SLDG_OK) return st;
       cur = 1 - cur;
@@ -968,6 +1057,30 @@ sldg_status sldg_split_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
   }
   if (result_buffer) *result_buffer = cur;
   return ok();
+}
+
+sldg_status sldg_split_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq, int nsteps,
+                             double* mass0, void* hi0, double* mass1, void* hi1,
+                             int* result_buffer) {
+  if (!p) return fail(SLDG_ERR_ARG, "plan is NULL");
+  if (nseq < 0 || nsteps < 0 || (nseq > 0 && !seq))
+    return fail(SLDG_ERR_ARG, "bad sweep sequence (nseq=%d nsteps=%d)", nseq, nsteps);
+  double* const m[2] = {mass0, mass1};
+  void* const h[2] = {hi0, hi1};
+  return run_steps(p, seq, nseq, nsteps, false, m, h, result_buffer);
+}
+
+sldg_status sldg_split_steps_adjoint(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq,
+                                     int nsteps, double* mass0, void* hi0, double* mass1,
+                                     void* hi1, int* result_buffer) {
+  if (!p) return fail(SLDG_ERR_ARG, "plan is NULL");
+  if (nseq < 0 || nsteps < 0 || (nseq > 0 && !seq))
+    return fail(SLDG_ERR_ARG, "bad sweep sequence (nseq=%d nsteps=%d)", nseq, nsteps);
+  std::vector<sldg_sweep_desc> rev((size_t)nseq);
+  for (int q = 0; q < nseq; ++q) rev[(size_t)q] = seq[nseq - 1 - q];
+  double* const m[2] = {mass0, mass1};
+  void* const h[2] = {hi0, hi1};
+  return run_steps(p, rev.data(), nseq, nsteps, true, m, h, result_buffer);
 }
 
 sldg_status sldg_advect_dims01(sldg_plan_t p, const double* shift0, uint32_t dep_mask0,

@@ -119,7 +119,7 @@ struct BatchItem {
 };
 
 // The line tables of up to kMaxTableSet sweeps computed in one launch
-// (forward tables, component-major): sweep q has first[q + 1] - first[q]
+// (component-major unless entry_major says otherwise): sweep q has first[q + 1] - first[q]
 // entries, period[q] cells along its dimension and displacements sigma[q].
 constexpr int kMaxTableSet = 16;
 struct TableSet {
@@ -127,6 +127,8 @@ struct TableSet {
   int64_t first[kMaxTableSet + 1];
   int64_t period[kMaxTableSet];
   const double* sigma[kMaxTableSet];
+  uint32_t entry_major;      // bit q: sweep q's table entry-major
+  uint32_t adjoint;          // bit q: the transposed sweep's table
 };
 
 // Launchers (defined in sldg_kernels.hip).  All return hipGetLastError().
@@ -161,6 +163,18 @@ hipError_t launch_xy(int k, int tier, const XYArgs& a, int64_t lds_bytes, int32_
                      hipStream_t st);
 template <int K, int TIER>
 hipError_t launch_xy_inst(const XYArgs& a, int64_t lds_bytes, int32_t nblocks, hipStream_t st);
+// X V X (post = 1) or V X X (post = 2) in one pass (sldg_strang.h): nblocks
+// waves; the batched form takes one wave per item of one degree.
+struct StrangArgs;
+hipError_t launch_strang(int k, int tier, int post, const StrangArgs& a, int32_t nblocks,
+                         hipStream_t st);
+hipError_t launch_batch_strang(int k, int tier, const StrangArgs* args, const BatchItem* items,
+                               int32_t nitems, int32_t xcd, hipStream_t st);
+template <int K, int TIER>
+hipError_t launch_strang_inst(int post, const StrangArgs& a, int32_t nblocks, hipStream_t st);
+template <int K, int TIER>
+hipError_t launch_batch_strang_inst(const StrangArgs* args, const BatchItem* items, int32_t nitems,
+                                    int32_t xcd, hipStream_t st);
 // Waves of one sweep launch that compute a given output plane (the absmax
 // partial slots per plane of a scaled FP16 sweep).
 int64_t sweep_slots(int dim, const SweepArgs& a);

@@ -119,21 +119,27 @@ __global__ __launch_bounds__(256) void line_tables_kernel(int64_t n, int64_t per
   line_table_entry<K, ADJ>(t, sigma[t], period, s_out, ab_out, cs, ts);
 }
 
-// The tables of several sweeps (forward, component-major) in one launch:
-// entry t of the flat range belongs to sweep q with first[q] <= t <
-// first[q + 1]; sweep q's table is the one line_tables_kernel writes, at
-// s_out + first[q] and ab_out + 2 (k+1)^2 first[q].
+// The tables of several sweeps in one launch: entry t of the flat range
+// belongs to sweep q with first[q] <= t < first[q + 1]; sweep q's table is the
+// one line_tables_kernel writes, at s_out + first[q] and
+// ab_out + 2 (k+1)^2 first[q].
 template <int K>
 __global__ __launch_bounds__(256) void line_tables_set_kernel(TableSet set,
                                                               int32_t* __restrict__ s_out,
                                                               double* __restrict__ ab_out) {
+  constexpr int64_t E = 2LL * (K + 1) * (K + 1);
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= set.first[set.count]) return;
   int q = 0;
   while (q + 1 < set.count && t >= set.first[q + 1]) ++q;
   const int64_t f = set.first[q], n = set.first[q + 1] - f;
-  line_table_entry<K, false>(t - f, set.sigma[q][t - f], set.period[q], s_out + f,
-                             ab_out + 2LL * (K + 1) * (K + 1) * f, n, 1);
+  const bool em = set.entry_major >> q & 1;
+  const double sg = set.sigma[q][t - f];
+  const int64_t cs = em ? 1 : n, ts = em ? E : 1;
+  if (set.adjoint >> q & 1)
+    line_table_entry<K, true>(t - f, sg, set.period[q], s_out + f, ab_out + E * f, cs, ts);
+  else
+    line_table_entry<K, false>(t - f, sg, set.period[q], s_out + f, ab_out + E * f, cs, ts);
 }
 
 hipError_t launch_line_tables(int k, int64_t n, int64_t period, const double* sigma,
@@ -254,6 +260,72 @@ hipError_t launch_xy(int k, int tier, const XYArgs& a, int64_t lds_bytes, int32_
       break;
   }
 #undef SLDG_XY_CALL
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_strang(int k, int tier, int post, const StrangArgs& a, int32_t nblocks,
+                         hipStream_t st) {
+#define SLDG_STRANG_CALL(KK, TT) launch_strang_inst<KK, TT>(post, a, nblocks, st)
+  switch (k) {
+    case 1:
+      switch (tier) {
+        case 0: return SLDG_STRANG_CALL(1, 0);
+        case 1: return SLDG_STRANG_CALL(1, 1);
+        case 2: return SLDG_STRANG_CALL(1, 2);
+        case 3: return SLDG_STRANG_CALL(1, 3);
+      }
+      break;
+    case 2:
+      switch (tier) {
+        case 0: return SLDG_STRANG_CALL(2, 0);
+        case 1: return SLDG_STRANG_CALL(2, 1);
+        case 2: return SLDG_STRANG_CALL(2, 2);
+        case 3: return SLDG_STRANG_CALL(2, 3);
+      }
+      break;
+    case 3:
+      switch (tier) {
+        case 0: return SLDG_STRANG_CALL(3, 0);
+        case 1: return SLDG_STRANG_CALL(3, 1);
+        case 2: return SLDG_STRANG_CALL(3, 2);
+        case 3: return SLDG_STRANG_CALL(3, 3);
+      }
+      break;
+  }
+#undef SLDG_STRANG_CALL
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_batch_strang(int k, int tier, const StrangArgs* args, const BatchItem* items,
+                               int32_t nitems, int32_t xcd, hipStream_t st) {
+#define SLDG_STRANG_CALL(KK, TT) launch_batch_strang_inst<KK, TT>(args, items, nitems, xcd, st)
+  switch (k) {
+    case 1:
+      switch (tier) {
+        case 0: return SLDG_STRANG_CALL(1, 0);
+        case 1: return SLDG_STRANG_CALL(1, 1);
+        case 2: return SLDG_STRANG_CALL(1, 2);
+        case 3: return SLDG_STRANG_CALL(1, 3);
+      }
+      break;
+    case 2:
+      switch (tier) {
+        case 0: return SLDG_STRANG_CALL(2, 0);
+        case 1: return SLDG_STRANG_CALL(2, 1);
+        case 2: return SLDG_STRANG_CALL(2, 2);
+        case 3: return SLDG_STRANG_CALL(2, 3);
+      }
+      break;
+    case 3:
+      switch (tier) {
+        case 0: return SLDG_STRANG_CALL(3, 0);
+        case 1: return SLDG_STRANG_CALL(3, 1);
+        case 2: return SLDG_STRANG_CALL(3, 2);
+        case 3: return SLDG_STRANG_CALL(3, 3);
+      }
+      break;
+  }
+#undef SLDG_STRANG_CALL
   return hipErrorInvalidValue;
 }
 
