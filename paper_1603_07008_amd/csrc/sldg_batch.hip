@@ -16,8 +16,17 @@
 
 #include "sldg.h"
 #include "sldg_internal.h"
+#include "sldg_strang.h"
 
 using namespace sldg;
+
+// A problem's part in an X V X pass (sweeps q, q + 1, q + 2 along dimensions
+// 0, 1, 0; sldg_strang.h): whether the pass takes it, and where the
+// entry-major matrices of its two X sweeps are.
+struct PassInfo {
+  bool on = false;
+  int64_t ab0 = 0, ab1 = 0;
+};
 
 struct sldg_batch_s {
   int nprob = 0, ndim = 0;
@@ -47,6 +56,17 @@ struct sldg_batch_s {
   std::vector<BatchItem*> d_items;
   std::vector<int32_t> nitems;
   std::vector<int32_t> cls_off;           // [nseq * (kClasses + 1)] class offsets in the list
+  // X V X passes: per first sweep q the problems taken, their arguments and
+  // items (by degree), and the work lists of the
+  // problems that run sweep by sweep
+  std::vector<char> triple;               // [nseq] a pass starts here
+  std::vector<PassInfo> pass;             // [nseq * nprob]
+  double* d_em = nullptr;                 // entry-major matrices of the passes' X sweeps
+  std::vector<StrangArgs*> d_pass_args;   // [nseq * 2]
+  std::vector<BatchItem*> d_pass_items;   // [nseq]
+  std::vector<int32_t> pass_off;          // [nseq * (kPassClasses + 1)]
+  std::vector<BatchItem*> d_rest;         // [nseq]
+  std::vector<int32_t> rest_off;          // [nseq * (kClasses + 1)]
   bool ready = false;
   hipGraphExec_t graph[2] = {nullptr, nullptr};
 };
@@ -55,12 +75,18 @@ namespace {
 
 // Work-list classes: kind (0 window, 1 group, 2 strided) x degree (1..3).
 constexpr int kClasses = 9;
+constexpr int kPassClasses = 3;
 int class_of(int kind, int k) { return kind * 3 + (k - 1); }
 
 // XCD run lengths of the class launches: twice those of the single-problem
 // sweeps (measured on the batched Landau workload: 2.50 ms per step against
 // 2.53 ms with 8 and 16).
 constexpr int32_t kXcdContigDefault = 16, kXcdStridedDefault = 32;
+
+// ... and of the X V X pass: the tiles of a strip and neighbouring strips share
+// cache lines and rows (512 problems, two steps: 1.97 ms with runs of 8, 1.92
+// with 24, 1.91 with 48; 2.24 ms in dispatch order).
+constexpr int32_t kXcdPass = 32;
 
 // XCD group sizes of the work lists (SLDG_BATCH_XCD_CONTIG / _STRIDED
 // override them, -1 .. 64).
@@ -88,6 +114,14 @@ void drop_graphs(sldg_batch_s* b) {
 void free_work(sldg_batch_s* b) {
   for (auto* p : b->d_args) if (p) dev_free(p);
   for (auto* p : b->d_items) if (p) dev_free(p);
+  for (auto* p : b->d_pass_args) if (p) dev_free(p);
+  for (auto* p : b->d_pass_items) if (p) dev_free(p);
+  for (auto* p : b->d_rest) if (p) dev_free(p);
+  b->d_pass_args.clear();
+  b->d_pass_items.clear();
+  b->pass_off.clear();
+  b->d_rest.clear();
+  b->rest_off.clear();
   b->d_args.clear();
   b->d_items.clear();
   b->nitems.clear();
@@ -101,6 +135,7 @@ void free_batch(sldg_batch_s* b) {
   free_work(b);
   if (b->d_s) dev_free(b->d_s);
   if (b->d_ab) dev_free(b->d_ab);
+  if (b->d_em) dev_free(b->d_em);
   if (b->d_pmap) dev_free(b->d_pmap);
   delete b;
 }
@@ -108,6 +143,25 @@ void free_batch(sldg_batch_s* b) {
 const int64_t* ext(const sldg_batch_s* b, int p) { return b->n.data() + (size_t)p * b->ndim; }
 
 bool aligned16(const void* x) { return ((uintptr_t)x & 15) == 0; }
+
+// The first sweep of the X V X pass that sweep q belongs to, or -1.
+int triple_of(const sldg_batch_s* b, int q) {
+  for (int f = std::max(0, q - 2); f <= q; ++f)
+    if (b->triple[(size_t)f]) return f;
+  return -1;
+}
+
+sldg_status upload_items(BatchItem*& d, const std::vector<BatchItem>& items, const char* what) {
+  if (d) {
+    dev_free(d);
+    d = nullptr;
+  }
+  if (items.empty()) return SLDG_OK;
+  hipError_t e = dev_malloc(&d, sizeof(BatchItem) * items.size());
+  if (e != hipSuccess) return fail(SLDG_ERR_NOMEM, "%s: %s", what, hipGetErrorString(e));
+  e = hipMemcpy(d, items.data(), sizeof(BatchItem) * items.size(), hipMemcpyHostToDevice);
+  return e == hipSuccess ? SLDG_OK : device_error(e, what);
+}
 
 // Build the device argument blocks and work list of sweep q.
 sldg_status build_sweep_impl(sldg_batch_s* b, int q) {
@@ -179,17 +233,25 @@ sldg_status build_sweep_impl(sldg_batch_s* b, int q) {
           for (int64_t x = 0; x < xt; ++x) bk.push_back({p, 2, (int32_t)x, qg, (int32_t)z});
     }
   }
-  std::vector<BatchItem> items;
-  std::vector<int32_t> off(kClasses + 1, 0);
+  std::vector<BatchItem> items, rest;
+  std::vector<int32_t> off(kClasses + 1, 0), roff(kClasses + 1, 0);
+  const int first = triple_of(b, q);
   for (int c = 0; c < kClasses; ++c) {
     off[c] = (int32_t)std::min<size_t>(items.size(), 0x7fffffff);
+    roff[c] = (int32_t)std::min<size_t>(rest.size(), 0x7fffffff);
     items.insert(items.end(), bucket[c].begin(), bucket[c].end());
+    if (first >= 0)
+      for (const BatchItem& w : bucket[c])
+        if (!b->pass[(size_t)first * b->nprob + w.prob].on) rest.push_back(w);
     if (bucket[c].size() > 0x7fffffff || items.size() > 0x7fffffff)
       return fail(SLDG_ERR_UNSUPPORTED, "work list too long");
   }
   off[kClasses] = (int32_t)items.size();
+  roff[kClasses] = (int32_t)rest.size();
   b->cls_off.resize((size_t)b->nseq * (kClasses + 1));
   std::copy(off.begin(), off.end(), b->cls_off.begin() + (size_t)q * (kClasses + 1));
+  b->rest_off.resize((size_t)b->nseq * (kClasses + 1));
+  std::copy(roff.begin(), roff.end(), b->rest_off.begin() + (size_t)q * (kClasses + 1));
   for (int s = 0; s < 2; ++s) {
     SweepArgs*& d = b->d_args[(size_t)q * 2 + s];
     if (!d) {
@@ -199,19 +261,86 @@ sldg_status build_sweep_impl(sldg_batch_s* b, int q) {
     hipError_t e = hipMemcpy(d, args[s].data(), sizeof(SweepArgs) * b->nprob, hipMemcpyHostToDevice);
     if (e != hipSuccess) return device_error(e, "batch arguments upload");
   }
-  BatchItem*& di = b->d_items[q];
-  if (di) {
-    dev_free(di);
-    di = nullptr;
-  }
-  if (!items.empty()) {
-    hipError_t e = dev_malloc(&di, sizeof(BatchItem) * items.size());
-    if (e != hipSuccess) return fail(SLDG_ERR_NOMEM, "batch work list: %s", hipGetErrorString(e));
-    e = hipMemcpy(di, items.data(), sizeof(BatchItem) * items.size(), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return device_error(e, "batch work list upload");
-  }
+  sldg_status st = upload_items(b->d_items[q], items, "batch work list");
+  if (st == SLDG_OK) st = upload_items(b->d_rest[q], rest, "batch work list");
+  if (st != SLDG_OK) return st;
   b->nitems[q] = (int32_t)items.size();
   return SLDG_OK;
+}
+
+// Rows per strip of the X V X pass.  A strip loads and X-sweeps three rows
+// more than it has, so 16 rows where that leaves the chip enough waves, else 8
+// (measured on 512 problems of 32-512 cells a side, 50,000 strips of 16: 1.92
+// ms for two steps with 16 rows, 1.89 with 8, 2.01 with 24; on 40 of them,
+// 4,000 strips: 0.220 ms with 16 rows, 0.196 with 8).
+int32_t pass_rows(const sldg_batch_s* b, int q) {
+  int64_t strips = 0;
+  for (int p = 0; p < b->nprob; ++p)
+    if (b->pass[(size_t)q * b->nprob + p].on)
+      strips += ((ext(b, p)[0] + 61) / 62) * ((ext(b, p)[1] + 15) / 16);
+  return strips >= 16384 ? 16 : 8;
+}
+
+// Device arguments and work list of the X V X pass that starts at sweep q.
+sldg_status build_pass(sldg_batch_s* b, int q) {
+  const int32_t rows = pass_rows(b, q);
+  std::vector<StrangArgs> args[2];
+  std::vector<BatchItem> bucket[kPassClasses];
+  for (int s = 0; s < 2; ++s) args[s].resize(b->nprob);
+  for (int p = 0; p < b->nprob; ++p) {
+    const PassInfo& pi = b->pass[(size_t)q * b->nprob + p];
+    if (!pi.on) continue;
+    const int k = b->k[p], o = k + 1;
+    const int64_t* n = ext(b, p);
+    StrangArgs x{};
+    x.n_lo = 1;
+    x.cells = b->cells[p];
+    x.N0 = (int32_t)n[0];
+    x.N1 = (int32_t)n[1];
+    x.Q = (int32_t)(b->cells[p] / (n[0] * n[1]));
+    strang_tiles(x, rows);
+    x.one = 1.0f;
+    LineTable* tab[3] = {&x.x0, &x.v, &x.x1};
+    for (int i = 0; i < 3; ++i) {
+      const size_t at = (size_t)(q + i) * b->nprob + p;
+      SweepArgs a{};
+      int64_t nt = 0;
+      describe_grid(b->ndim, n, o, b->modes[p], i == 1 ? 1 : 0, b->masks[at], 4, 0, a, nt);
+      const double* ab = i == 1 ? b->d_ab + b->ab_off[at] : b->d_em + (i == 0 ? pi.ab0 : pi.ab1);
+      *tab[i] = {b->d_s + b->tab_off[at], ab, i == 1 ? nt : 1, i == 1 ? 1 : 2LL * o * o,
+                 (int32_t)(b->masks[at] >> (i == 1 ? 0 : 1) & 1), a.map};
+    }
+    for (int src = 0; src < 2; ++src) {
+      x.in_lo = b->mass[src][p];
+      x.in_hi = b->hi[src][p];
+      x.out_lo = b->mass[1 - src][p];
+      x.out_hi = b->hi[1 - src][p];
+      args[src][p] = x;
+    }
+    auto& bk = bucket[k - 1];
+    const int64_t groups = b->modes[p] / (o * o);
+    for (int64_t g = 0; g < groups; ++g)
+      for (int32_t z = 0; z < x.Q; ++z)
+        for (int32_t w = 0; w < x.nstrip; ++w)
+          for (int32_t t = 0; t < x.ntile; ++t) bk.push_back({p, t, w, (int32_t)g, z});
+  }
+  std::vector<BatchItem> items;
+  b->pass_off.resize((size_t)b->nseq * (kPassClasses + 1), 0);
+  int32_t* off = b->pass_off.data() + (size_t)q * (kPassClasses + 1);
+  for (int c = 0; c < kPassClasses; ++c) {
+    off[c] = (int32_t)items.size();
+    items.insert(items.end(), bucket[c].begin(), bucket[c].end());
+    if (items.size() > 0x7fffffff) return fail(SLDG_ERR_UNSUPPORTED, "work list too long");
+  }
+  off[kPassClasses] = (int32_t)items.size();
+  for (int s = 0; s < 2 && !items.empty(); ++s) {
+    StrangArgs*& d = b->d_pass_args[(size_t)q * 2 + s];
+    hipError_t e = d ? hipSuccess : dev_malloc(&d, sizeof(StrangArgs) * b->nprob);
+    if (e != hipSuccess) return fail(SLDG_ERR_NOMEM, "batch arguments: %s", hipGetErrorString(e));
+    e = hipMemcpy(d, args[s].data(), sizeof(StrangArgs) * b->nprob, hipMemcpyHostToDevice);
+    if (e != hipSuccess) return device_error(e, "batch arguments upload");
+  }
+  return upload_items(b->d_pass_items[q], items, "batch work list");
 }
 
 // A sweep whose work list could not be built leaves the batch not ready (run
@@ -229,24 +358,59 @@ sldg_status build_all(sldg_batch_s* b) {
   b->d_args.resize((size_t)b->nseq * 2, nullptr);
   b->d_items.resize(b->nseq, nullptr);
   b->nitems.resize(b->nseq, 0);
+  b->d_rest.resize(b->nseq, nullptr);
+  b->d_pass_args.resize((size_t)b->nseq * 2, nullptr);
+  b->d_pass_items.resize(b->nseq, nullptr);
   for (int q = 0; q < b->nseq; ++q) {
     sldg_status st = build_sweep(b, q);
+    if (st == SLDG_OK && b->triple[(size_t)q]) st = build_pass(b, q);
     if (st != SLDG_OK) return st;
   }
   b->ready = true;
   return SLDG_OK;
 }
 
-sldg_status launch(sldg_batch_s* b, int q, int src) {
-  const int32_t* off = b->cls_off.data() + (size_t)q * (kClasses + 1);
+// One sweep: of every problem, or (rest) of those no X V X pass takes.
+sldg_status launch(sldg_batch_s* b, int q, int src, bool rest = false) {
+  const int32_t* off = (rest ? b->rest_off : b->cls_off).data() + (size_t)q * (kClasses + 1);
+  const BatchItem* list = rest ? b->d_rest[q] : b->d_items[q];
   for (int c = 0; c < kClasses; ++c) {
     const int32_t n = off[c + 1] - off[c];
     if (n <= 0) continue;
     const int kind = c / 3, k = c % 3 + 1;
     hipError_t e = launch_batch_class((int)b->tier, k, kind, b->rows[(size_t)q * kClasses + c],
-                                      b->d_args[(size_t)q * 2 + src], b->d_items[q] + off[c], n,
+                                      b->d_args[(size_t)q * 2 + src], list + off[c], n,
                                       xcd_group(kind == 2), b->stream);
     if (e != hipSuccess) return device_error(e, "batched sweep launch");
+  }
+  return SLDG_OK;
+}
+
+// One split step from buffer `cur`, which moves on to the buffer holding the
+// result (three sweeps and one X V X pass end in the same one).
+sldg_status launch_step(sldg_batch_s* b, int& cur) {
+  for (int q = 0; q < b->nseq; ++q) {
+    sldg_status st = SLDG_OK;
+    if (b->triple[(size_t)q]) {
+      const int32_t* off = b->pass_off.data() + (size_t)q * (kPassClasses + 1);
+      for (int c = kPassClasses - 1; c >= 0; --c) {
+        const int32_t n = off[c + 1] - off[c];
+        if (n <= 0) continue;
+        const hipError_t e =
+            launch_batch_strang(c + 1, (int)b->tier, b->d_pass_args[(size_t)q * 2 + cur],
+                                b->d_pass_items[q] + off[c], n, kXcdPass, b->stream);
+        if (e != hipSuccess) return device_error(e, "batched X V X launch");
+      }
+      for (int i = 0; i < 3 && st == SLDG_OK; ++i) {
+        st = launch(b, q + i, cur, true);
+        cur = 1 - cur;
+      }
+      q += 2;
+    } else {
+      st = launch(b, q, cur);
+      cur = 1 - cur;
+    }
+    if (st != SLDG_OK) return st;
   }
   return SLDG_OK;
 }
@@ -361,8 +525,10 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
   free_work(b);
   if (b->d_s) dev_free(b->d_s);
   if (b->d_ab) dev_free(b->d_ab);
+  if (b->d_em) dev_free(b->d_em);
   b->d_s = nullptr;
   b->d_ab = nullptr;
+  b->d_em = nullptr;
   b->nseq = nseq;
   b->dims.assign(dims, dims + nseq);
   b->masks.assign(masks, masks + (size_t)nseq * b->nprob);
@@ -388,8 +554,10 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
   auto drop_sequence = [&](sldg_status st) {
     if (b->d_s) dev_free(b->d_s);
     if (b->d_ab) dev_free(b->d_ab);
+    if (b->d_em) dev_free(b->d_em);
     b->d_s = nullptr;
     b->d_ab = nullptr;
+    b->d_em = nullptr;
     b->nseq = 0;
     return st;
   };
@@ -405,6 +573,45 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
                              b->stream);
       if (e != hipSuccess) return drop_sequence(device_error(e, "batch line tables"));
     }
+  // X V X passes, and the entry-major matrices of their X sweeps
+  b->triple.assign((size_t)nseq, 0);
+  b->pass.assign((size_t)nseq * b->nprob, PassInfo{});
+  int64_t tot_em = 0;
+  for (int q = 0; q + 2 < nseq; ++q) {
+    if (dims[q] != 0 || dims[q + 1] != 1 || dims[q + 2] != 0) continue;
+    for (int p = 0; p < b->nprob; ++p) {
+      if (!strang_fits(b->cells[p], b->k[p] + 1, elem_size(b->tier))) continue;
+      PassInfo& pi = b->pass[(size_t)q * b->nprob + p];
+      pi.on = true;
+      b->triple[(size_t)q] = 1;
+      const int64_t E = 2LL * (b->k[p] + 1) * (b->k[p] + 1);
+      const size_t i0 = (size_t)q * b->nprob + p, i1 = i0 + 2 * (size_t)b->nprob;
+      pi.ab0 = pi.ab1 = tot_em;
+      tot_em += E * b->tab_n[i0];
+      if (shifts[i0] != shifts[i1] || b->masks[i0] != b->masks[i1]) {
+        pi.ab1 = tot_em;
+        tot_em += E * b->tab_n[i1];
+      }
+    }
+    if (b->triple[(size_t)q]) q += 2;
+  }
+  if (tot_em > 0) {
+    e = dev_malloc(&b->d_em, sizeof(double) * tot_em);
+    if (e != hipSuccess)
+      return drop_sequence(fail(SLDG_ERR_NOMEM, "batch tables: %s", hipGetErrorString(e)));
+    for (int q = 0; q < nseq; ++q)
+      for (int p = 0; p < b->nprob && b->triple[(size_t)q]; ++p) {
+        const PassInfo& pi = b->pass[(size_t)q * b->nprob + p];
+        if (!pi.on) continue;
+        for (int i = 0; i < (pi.ab1 != pi.ab0 ? 2 : 1); ++i) {
+          const size_t at = (size_t)(q + 2 * i) * b->nprob + p;
+          e = launch_line_tables(b->k[p], b->tab_n[at], ext(b, p)[0], shifts[at],
+                                 b->d_s + b->tab_off[at], b->d_em + (i ? pi.ab1 : pi.ab0), false,
+                                 false, b->stream);
+          if (e != hipSuccess) return drop_sequence(device_error(e, "batch line tables"));
+        }
+      }
+  }
   b->rows.assign((size_t)nseq * kClasses, 4);
   b->tuples.assign((size_t)nseq * kClasses, 9);
   b->tuned_ms.assign((size_t)nseq * kClasses, -1.0);
@@ -425,11 +632,8 @@ sldg_status sldg_batch_run(sldg_batch_t b, int nsteps, int use_graph, int* resul
         hipError_t e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return device_error(e, "hipStreamBeginCapture");
         int c = cur;
-        sldg_status st = SLDG_OK;
-        for (int q = 0; q < b->nseq && st == SLDG_OK; ++q) {
-          st = launch(b, q, c);
-          c = 1 - c;
-        }
+        sldg_status st;
+        st = launch_step(b, c);
         e = hipStreamEndCapture(b->stream, &g);
         if (st != SLDG_OK) {
           if (g) (void)hipGraphDestroy(g);
@@ -445,12 +649,10 @@ sldg_status sldg_batch_run(sldg_batch_t b, int nsteps, int use_graph, int* resul
       if (b->nseq % 2) cur = 1 - cur;
     }
   } else {
-    for (int n = 0; n < nsteps; ++n)
-      for (int q = 0; q < b->nseq; ++q) {
-        sldg_status st = launch(b, q, cur);
-        if (st != SLDG_OK) return st;
-        cur = 1 - cur;
-      }
+    for (int n = 0; n < nsteps; ++n) {
+      sldg_status st = launch_step(b, cur);
+      if (st != SLDG_OK) return st;
+    }
   }
   if (result_buffer) *result_buffer = cur;
   return ok();
