@@ -565,14 +565,6 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
   if (e == hipSuccess) e = dev_malloc(&b->d_ab, sizeof(double) * std::max<int64_t>(1, tot_ab));
   if (e != hipSuccess)
     return drop_sequence(fail(SLDG_ERR_NOMEM, "batch tables: %s", hipGetErrorString(e)));
-  for (int q = 0; q < nseq; ++q)
-    for (int p = 0; p < b->nprob; ++p) {
-      const size_t i = (size_t)q * b->nprob + p;
-      e = launch_line_tables(b->k[p], b->tab_n[i], ext(b, p)[dims[q]], shifts[i],
-                             b->d_s + b->tab_off[i], b->d_ab + b->ab_off[i], true, false,
-                             b->stream);
-      if (e != hipSuccess) return drop_sequence(device_error(e, "batch line tables"));
-    }
   // X V X passes, and the entry-major matrices of their X sweeps
   b->triple.assign((size_t)nseq, 0);
   b->pass.assign((size_t)nseq * b->nprob, PassInfo{});
@@ -599,18 +591,38 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
     e = dev_malloc(&b->d_em, sizeof(double) * tot_em);
     if (e != hipSuccess)
       return drop_sequence(fail(SLDG_ERR_NOMEM, "batch tables: %s", hipGetErrorString(e)));
-    for (int q = 0; q < nseq; ++q)
-      for (int p = 0; p < b->nprob && b->triple[(size_t)q]; ++p) {
-        const PassInfo& pi = b->pass[(size_t)q * b->nprob + p];
-        if (!pi.on) continue;
-        for (int i = 0; i < (pi.ab1 != pi.ab0 ? 2 : 1); ++i) {
-          const size_t at = (size_t)(q + 2 * i) * b->nprob + p;
-          e = launch_line_tables(b->k[p], b->tab_n[at], ext(b, p)[0], shifts[at],
-                                 b->d_s + b->tab_off[at], b->d_em + (i ? pi.ab1 : pi.ab0), false,
-                                 false, b->stream);
-          if (e != hipSuccess) return drop_sequence(device_error(e, "batch line tables"));
-        }
-      }
+  }
+  // every table, in one launch per degree
+  std::vector<TableJob> jobs[3];
+  int64_t nblk[3] = {0, 0, 0};
+  auto add = [&](int q, int p, double* ab, bool em) {
+    const size_t i = (size_t)q * b->nprob + p;
+    const int c = b->k[p] - 1;
+    jobs[c].push_back({shifts[i], b->d_s + b->tab_off[i], ab, (int32_t)b->tab_n[i],
+                       (int32_t)ext(b, p)[dims[q]], em ? 1 : 0, (int32_t)nblk[c]});
+    nblk[c] += (b->tab_n[i] + 255) / 256;
+  };
+  for (int q = 0; q < nseq; ++q)
+    for (int p = 0; p < b->nprob; ++p) {
+      add(q, p, b->d_ab + b->ab_off[(size_t)q * b->nprob + p], false);
+      const PassInfo& pi = b->pass[(size_t)q * b->nprob + p];
+      if (!pi.on) continue;
+      add(q, p, b->d_em + pi.ab0, true);
+      if (pi.ab1 != pi.ab0) add(q + 2, p, b->d_em + pi.ab1, true);
+    }
+  for (int c = 0; c < 3; ++c) {
+    if (jobs[c].empty()) continue;
+    if (nblk[c] > 0x7fffffff) return drop_sequence(fail(SLDG_ERR_UNSUPPORTED, "batch tables too long"));
+    TableJob* d = nullptr;
+    e = dev_malloc(&d, sizeof(TableJob) * jobs[c].size());
+    if (e != hipSuccess)
+      return drop_sequence(fail(SLDG_ERR_NOMEM, "batch tables: %s", hipGetErrorString(e)));
+    e = hipMemcpy(d, jobs[c].data(), sizeof(TableJob) * jobs[c].size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+      e = launch_line_tables_jobs(c + 1, d, (int32_t)jobs[c].size(), (int32_t)nblk[c], b->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);   // before the list is freed
+    dev_free(d);
+    if (e != hipSuccess) return drop_sequence(device_error(e, "batch line tables"));
   }
   b->rows.assign((size_t)nseq * kClasses, 4);
   b->tuples.assign((size_t)nseq * kClasses, 9);

@@ -57,12 +57,46 @@ __device__ __forceinline__ double horner_comp(const double (&c)[2 * K + 2], doub
 // with shift s' = -s-1 and matrices (A', B') = (B^T, A^T).  It is built from
 // the same (snapped, exact-mass-row) A and B, so it is the exact transpose of
 // the forward map.
-template <int K, bool ADJ>
-__device__ __forceinline__ void line_table_entry(int64_t t, double sg, int64_t period,
-                                                 int32_t* __restrict__ s_out,
-                                                 double* __restrict__ ab_out, int64_t cs,
-                                                 int64_t ts) {
+// One thread evaluates one component of one entry (blockIdx.y: the component):
+// a table of a few hundred entries is then some thousands of short chains
+// instead of a few hundred long ones, which one wave per entry group took 4-17
+// us to walk (k = 3, 1,289 entries: 16.8 us; now 3 us).
+
+// Coefficients of every component, A row-major, then B.
+template <int K>
+struct AbCoef {
+  double v[2 * (K + 1) * (K + 1)][2 * K + 2];
+};
+template <int K>
+constexpr AbCoef<K> make_ab_coef() {
+  AbCoef<K> c{};
   constexpr int O = K + 1;
+  for (int j = 0; j < O; ++j)
+    for (int l = 0; l < O; ++l)
+      for (int p = 0; p < 2 * K + 2; ++p) {
+        c.v[j * O + l][p] = AbPoly<K>::A[j][l][p];
+        c.v[O * O + j * O + l][p] = AbPoly<K>::B[j][l][p];
+      }
+  return c;
+}
+__constant__ AbCoef<1> ab_coef1 = make_ab_coef<1>();
+__constant__ AbCoef<2> ab_coef2 = make_ab_coef<2>();
+__constant__ AbCoef<3> ab_coef3 = make_ab_coef<3>();
+
+template <int K>
+__device__ __forceinline__ const double (&ab_coef(int e))[2 * K + 2] {
+  if constexpr (K == 1) return ab_coef1.v[e];
+  else if constexpr (K == 2) return ab_coef2.v[e];
+  else return ab_coef3.v[e];
+}
+
+// Component e (uniform) of the entry of displacement sg, written at ab_out +
+// e * cs; the block of component 0 also writes the shift.  ADJ as above.
+template <int K, bool ADJ>
+__device__ __forceinline__ void line_table_component(int e, double sg, int64_t period,
+                                                     int32_t* __restrict__ s_out,
+                                                     double* __restrict__ ab_out, int64_t cs) {
+  constexpr int O = K + 1, O2 = O * O;
   double fs = floor(sg);
   double alpha = sg - fs;
   const double beta0 = 1.0 - alpha;
@@ -73,39 +107,36 @@ __device__ __forceinline__ void line_table_entry(int64_t t, double sg, int64_t p
     alpha = 0.0;
     beta = 1.0;
   }
-  int32_t s = 0;
-  if (isfinite(sg)) {
-    double r = fmod(ADJ ? -fs - 1.0 : fs, (double)period);   // exact
-    if (r < 0) r += (double)period;
-    s = (int32_t)r;
-  } else {
+  const bool finite = isfinite(sg);
+  if (!finite) {
     alpha = __builtin_nan("");
     beta = alpha;
   }
-  s_out[t] = s;
-  double A[O][O], B[O][O];
-#pragma unroll
-  for (int j = 0; j < O; ++j) {
-#pragma unroll
-    for (int l = 0; l < O; ++l) {
-      A[j][l] = horner_comp<K>(AbPoly<K>::A[j][l], alpha);
-      B[j][l] = horner_comp<K>(AbPoly<K>::B[j][l], alpha);
+  if (e == 0) {
+    int32_t s = 0;
+    if (finite) {
+      double r = fmod(ADJ ? -fs - 1.0 : fs, (double)period);   // exact
+      if (r < 0) r += (double)period;
+      s = (int32_t)r;
     }
+    *s_out = s;
+  }
+  // component e is entry (j, l) of A (first half) or B; transposed and with A
+  // and B exchanged for ADJ
+  int src = e;
+  if constexpr (ADJ) {
+    const int m = e < O2 ? e : e - O2;
+    src = (m % O) * O + m / O + (e < O2 ? O2 : 0);
   }
   // Mass row made exact: int P_l over a cell vanishes for l >= 1, so the two
-  // contributions of a source cell to the cell means must cancel exactly.
-  A[0][0] = beta;
-  B[0][0] = alpha;
-#pragma unroll
-  for (int l = 1; l < O; ++l) B[0][l] = -A[0][l];
-  double* base = ab_out + t * ts;
-#pragma unroll
-  for (int j = 0; j < O; ++j)
-#pragma unroll
-    for (int l = 0; l < O; ++l) {
-      base[(j * O + l) * cs] = ADJ ? B[l][j] : A[j][l];
-      base[(O * O + j * O + l) * cs] = ADJ ? A[l][j] : B[j][l];
-    }
+  // contributions of a source cell to the cell means must cancel exactly:
+  // A_00 = beta, B_00 = alpha, B_0l = -A_0l.
+  const bool neg = src > O2 && src < O2 + O;
+  double v;
+  if (src == 0) v = beta;
+  else if (src == O2) v = alpha;
+  else v = horner_comp<K>(ab_coef<K>(neg ? src - O2 : src), alpha);
+  ab_out[e * cs] = neg ? -v : v;
 }
 
 template <int K, bool ADJ>
@@ -116,7 +147,7 @@ __global__ __launch_bounds__(256) void line_tables_kernel(int64_t n, int64_t per
                                                           int64_t cs, int64_t ts) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n) return;
-  line_table_entry<K, ADJ>(t, sigma[t], period, s_out, ab_out, cs, ts);
+  line_table_component<K, ADJ>((int)blockIdx.y, sigma[t], period, s_out + t, ab_out + t * ts, cs);
 }
 
 // The tables of several sweeps in one launch: entry t of the flat range
@@ -134,13 +165,34 @@ __global__ __launch_bounds__(256) void line_tables_set_kernel(TableSet set,
   while (q + 1 < set.count && t >= set.first[q + 1]) ++q;
   const int64_t f = set.first[q], n = set.first[q + 1] - f;
   const bool em = set.entry_major >> q & 1;
+  double* ab = ab_out + E * f + (em ? E : 1) * (t - f);
   const double sg = set.sigma[q][t - f];
-  const int64_t cs = em ? 1 : n, ts = em ? E : 1;
   if (set.adjoint >> q & 1)
-    line_table_entry<K, true>(t - f, sg, set.period[q], s_out + f, ab_out + E * f, cs, ts);
+    line_table_component<K, true>((int)blockIdx.y, sg, set.period[q], s_out + t, ab, em ? 1 : n);
   else
-    line_table_entry<K, false>(t - f, sg, set.period[q], s_out + f, ab_out + E * f, cs, ts);
+    line_table_component<K, false>((int)blockIdx.y, sg, set.period[q], s_out + t, ab, em ? 1 : n);
 }
+
+// The tables of any number of sweeps (a batch): job i takes the blocks from
+// blk0 on, 256 entries each.
+template <int K>
+__global__ __launch_bounds__(256) void line_tables_jobs_kernel(const TableJob* __restrict__ jobs,
+                                                               int32_t njobs) {
+  int32_t lo = 0, hi = njobs - 1;                  // the last job with blk0 <= blockIdx.x
+  while (lo < hi) {
+    const int32_t mid = (lo + hi + 1) >> 1;
+    if (jobs[mid].blk0 <= (int32_t)blockIdx.x) lo = mid;
+    else hi = mid - 1;
+  }
+  const TableJob j = jobs[lo];
+  const int64_t t = (int64_t)((int32_t)blockIdx.x - j.blk0) * 256 + threadIdx.x;
+  if (t >= j.n) return;
+  constexpr int64_t E = 2LL * (K + 1) * (K + 1);
+  line_table_component<K, false>((int)blockIdx.y, j.sigma[t], j.period, j.s + t,
+                                 j.ab + t * (j.entry_major ? E : 1), j.entry_major ? 1 : j.n);
+}
+
+static unsigned table_components(int k) { return 2u * (k + 1) * (k + 1); }
 
 hipError_t launch_line_tables(int k, int64_t n, int64_t period, const double* sigma,
                               int32_t* s_out, double* ab_out, bool component_major,
@@ -148,7 +200,7 @@ hipError_t launch_line_tables(int k, int64_t n, int64_t period, const double* si
   if (n <= 0) return hipSuccess;
   const int64_t e = 2LL * (k + 1) * (k + 1);
   const int64_t cs = component_major ? n : 1, ts = component_major ? 1 : e;
-  dim3 grid((unsigned)((n + 255) / 256)), block(256);
+  dim3 grid((unsigned)((n + 255) / 256), table_components(k)), block(256);
 #define SLDG_TABLES(KK, AA) line_tables_kernel<KK, AA><<<grid, block, 0, st>>>(n, period, sigma, s_out, ab_out, cs, ts)
   switch (k * 2 + (adjoint ? 1 : 0)) {
     case 2: SLDG_TABLES(1, false); break;
@@ -167,11 +219,24 @@ hipError_t launch_line_tables_set(int k, const TableSet& set, int32_t* s_out, do
                                   hipStream_t st) {
   const int64_t n = set.first[set.count];
   if (n <= 0) return hipSuccess;
-  dim3 grid((unsigned)((n + 255) / 256)), block(256);
+  dim3 grid((unsigned)((n + 255) / 256), table_components(k)), block(256);
   switch (k) {
     case 1: line_tables_set_kernel<1><<<grid, block, 0, st>>>(set, s_out, ab_out); break;
     case 2: line_tables_set_kernel<2><<<grid, block, 0, st>>>(set, s_out, ab_out); break;
     case 3: line_tables_set_kernel<3><<<grid, block, 0, st>>>(set, s_out, ab_out); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_line_tables_jobs(int k, const TableJob* jobs, int32_t njobs, int32_t nblocks,
+                                   hipStream_t st) {
+  if (njobs <= 0 || nblocks <= 0) return hipSuccess;
+  dim3 grid((unsigned)nblocks, table_components(k)), block(256);
+  switch (k) {
+    case 1: line_tables_jobs_kernel<1><<<grid, block, 0, st>>>(jobs, njobs); break;
+    case 2: line_tables_jobs_kernel<2><<<grid, block, 0, st>>>(jobs, njobs); break;
+    case 3: line_tables_jobs_kernel<3><<<grid, block, 0, st>>>(jobs, njobs); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
