@@ -24,38 +24,85 @@ __device__ __forceinline__ double as_double(T v) {
 }
 
 // Partial v-sums of the (j, 0) modes: workgroup (x, j, z) sums v rows
-// [z * rows, (z+1) * rows) of x cells [256x, 256x+256) of mode j.
+// [z * rows, (z+1) * rows) of x cells [64x, 64x+64) of mode j.  Each of its 16
+// waves sums every 16th row, and the waves' sums meet in LDS in a fixed order.
+// (One thread per x cell and chunk left 48 workgroups on a 512^2 grid, each a
+// chain of 64 loads: 17.5 us against 4 us.)
+constexpr int kDensityWaves = 16;
+
 template <class T>
-__global__ __launch_bounds__(256) void density_partial_kernel(FieldPlanes fp, int32_t nx,
-                                                              int32_t nv, int32_t rows,
-                                                              double* __restrict__ part) {
-  const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-  const int32_t j = (int32_t)blockIdx.y, z = (int32_t)blockIdx.z;
-  if (i >= nx) return;
-  const int32_t v0 = z * rows, v1 = min(nv, v0 + rows);
-  double acc = 0.0;
-  if (fp.lo[j]) {
-    const double* p = static_cast<const double*>(fp.plane[j]);
-    for (int32_t iv = v0; iv < v1; ++iv) acc += p[(int64_t)iv * nx + i];
-  } else {
-    const T* p = static_cast<const T*>(fp.plane[j]);
-    for (int32_t iv = v0; iv < v1; ++iv) acc += as_double(p[(int64_t)iv * nx + i]);
+__device__ __forceinline__ double column_sum(const T* __restrict__ p, int64_t stride, int64_t r0,
+                                             int64_t r1, int64_t i, bool live, double* sh) {
+  const int32_t c = (int32_t)(threadIdx.x & 63), w = (int32_t)(threadIdx.x >> 6);
+  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;  // four loads in flight
+  if (live) {
+    int64_t r = r0 + w;
+    for (; r + 3 * kDensityWaves < r1; r += 4 * kDensityWaves) {
+      const T v0 = p[r * stride + i], v1 = p[(r + kDensityWaves) * stride + i];
+      const T v2 = p[(r + 2 * kDensityWaves) * stride + i];
+      const T v3 = p[(r + 3 * kDensityWaves) * stride + i];
+      a0 += as_double(v0);
+      a1 += as_double(v1);
+      a2 += as_double(v2);
+      a3 += as_double(v3);
+    }
+    for (; r < r1; r += kDensityWaves) a0 += as_double(p[r * stride + i]);
   }
-  part[((int64_t)z * gridDim.y + j) * nx + i] = acc;
+  sh[threadIdx.x] = (a0 + a1) + (a2 + a3);
+  __syncthreads();
+  double sum = 0.0;
+  if (w == 0)
+#pragma unroll
+    for (int v = 0; v < kDensityWaves; ++v) sum += sh[v * 64 + c];
+  return sum;                                     // in the first wave
+}
+
+template <class T>
+__global__ __launch_bounds__(64 * kDensityWaves) void density_partial_kernel(
+    FieldPlanes fp, int32_t nx, int32_t nv, int32_t rows, double* __restrict__ part) {
+  __shared__ double sh[64 * kDensityWaves];
+  const int32_t i = (int32_t)(blockIdx.x * 64 + (threadIdx.x & 63));
+  const int32_t j = (int32_t)blockIdx.y, z = (int32_t)blockIdx.z;
+  const int32_t v0 = z * rows, v1 = min(nv, v0 + rows);
+  const double s =
+      fp.lo[j] ? column_sum(static_cast<const double*>(fp.plane[j]), nx, v0, v1, i, i < nx, sh)
+               : column_sum(static_cast<const T*>(fp.plane[j]), nx, v0, v1, i, i < nx, sh);
+  if (threadIdx.x < 64 && i < nx) part[((int64_t)z * gridDim.y + j) * nx + i] = s;
 }
 
 constexpr int kFieldThreads = 1024;
+constexpr int kFieldWaves = kFieldThreads / 64;
 
+// Sum over the workgroup, in every thread (fixed order: lane halves, then the
+// waves in turn).
 __device__ double block_sum(double v, double* sh) {
-  sh[threadIdx.x] = v;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int w = kFieldThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
-  }
-  const double r = sh[0];
+  double r = 0.0;
+#pragma unroll
+  for (int w = 0; w < kFieldWaves; ++w) r += sh[w];
   __syncthreads();
   return r;
+}
+
+// Sum of v over the threads below this one.
+__device__ double block_scan(double v, double* sh) {
+  const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
+  double inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double t = __shfl_up(inc, o);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) sh[wave] = inc;
+  __syncthreads();
+  double before = 0.0;
+  for (int w = 0; w < wave; ++w) before += sh[w];
+  __syncthreads();
+  const double prev = __shfl_up(inc, 1);
+  return before + (lane > 0 ? prev : 0.0);
 }
 
 // One workgroup: the density moments, the mean density, the face values of
@@ -66,7 +113,7 @@ __global__ __launch_bounds__(kFieldThreads) void field_solve_kernel(
     const double* __restrict__ part, int32_t nz, int32_t o, int32_t nx, double hx, double hv,
     double dt, double h0, double h1, double h2, double h3, double* __restrict__ r,
     double* __restrict__ faces, double* __restrict__ shift_out, double* __restrict__ field_out) {
-  __shared__ double sh[kFieldThreads];
+  __shared__ double sh[kFieldWaves];
   const double half[4] = {h0, h1, h2, h3};
   // density moments r[j][i] = h_v * sum over the v chunks
   for (int32_t i = threadIdx.x; i < nx; i += kFieldThreads)
@@ -80,23 +127,14 @@ __global__ __launch_bounds__(kFieldThreads) void field_solve_kernel(
   for (int32_t i = threadIdx.x; i < nx; i += kFieldThreads) loc += r[i];
   const double rbar = block_sum(loc, sh) / nx;
   // face values of the antiderivative of rho - rbar, from 0 at the left end:
-  // each thread sums a contiguous chunk of cells, an inclusive scan of the
-  // chunk sums (fixed order) gives each chunk's starting face, and the thread
-  // writes its chunk's faces
+  // each thread sums a contiguous chunk of cells, a scan of the chunk sums
+  // (fixed order) gives each chunk's starting face, and the thread writes its
+  // chunk's faces
   const int32_t per = (nx + kFieldThreads - 1) / kFieldThreads;
   const int32_t i0 = min(nx, (int32_t)threadIdx.x * per), i1 = min(nx, i0 + per);
   double chunk = 0.0;
   for (int32_t i = i0; i < i1; ++i) chunk += hx * (r[i] - rbar);
-  sh[threadIdx.x] = chunk;
-  __syncthreads();
-  for (int off = 1; off < kFieldThreads; off <<= 1) {
-    const double v = (int)threadIdx.x >= off ? sh[threadIdx.x - off] : 0.0;
-    __syncthreads();
-    sh[threadIdx.x] += v;
-    __syncthreads();
-  }
-  double f = threadIdx.x > 0 ? sh[threadIdx.x - 1] : 0.0;   // sum of the chunks before
-  __syncthreads();
+  double f = block_scan(chunk, sh);               // sum of the chunks before
   if (threadIdx.x == 0) faces[0] = 0.0;
   for (int32_t i = i0; i < i1; ++i) {
     f += hx * (r[i] - rbar);
@@ -117,6 +155,45 @@ __global__ __launch_bounds__(kFieldThreads) void field_solve_kernel(
   }
 }
 
+// The same for at most one x cell per thread and at most 8 chunks: the moments
+// and faces stay in registers and every partial sum is loaded at once (the
+// general form's dependent loads and passes through memory took 11.7 us at N_x =
+// 512).
+__global__ __launch_bounds__(kFieldThreads) void field_solve_line_kernel(
+    const double* __restrict__ part, int32_t nz, int32_t o, int32_t nx, double hx, double hv,
+    double dt, double h0, double h1, double h2, double h3, double* __restrict__ shift_out,
+    double* __restrict__ field_out) {
+  __shared__ double sh[kFieldWaves];
+  const double half[4] = {h0, h1, h2, h3};
+  const int32_t i = (int32_t)threadIdx.x;
+  const bool live = i < nx;
+  double p[4][8];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int z = 0; z < 8; ++z)
+      p[j][z] = live && j < o && z < nz ? part[((int64_t)z * o + j) * nx + i] : 0.0;
+  double r[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    double acc = 0.0;
+#pragma unroll
+    for (int z = 0; z < 8; ++z) acc += p[j][z];
+    r[j] = hv * acc;
+  }
+  const double rbar = block_sum(r[0], sh) / nx;
+  const double d = live ? r[0] - rbar : 0.0;
+  const double face = block_scan(hx * d, sh);
+  const double C = -block_sum(live ? face + 0.5 * hx * d - hx / 6.0 * r[1] : 0.0, sh) / nx;
+  if (!live) return;
+  double g = d * half[0];
+#pragma unroll
+  for (int j = 1; j < 4; ++j) g += r[j] * half[j];
+  const double E = face + C + 0.5 * hx * g;
+  shift_out[i] = E * dt / hv;
+  if (field_out) field_out[i] = E;
+}
+
 template <class T>
 static hipError_t launch_field_t(const FieldPlanes& fp, int o, int32_t nx, int32_t nv,
                                  double hx, double hv, double dt, double* scratch,
@@ -126,12 +203,16 @@ static hipError_t launch_field_t(const FieldPlanes& fp, int o, int32_t nx, int32
   double* part = scratch;                                  // [nz][o][nx]
   double* r = part + (int64_t)nz * o * nx;                 // [o][nx]
   double* faces = r + (int64_t)o * nx;                     // [nx + 1]
-  dim3 grid((unsigned)((nx + 255) / 256), (unsigned)o, (unsigned)nz);
-  density_partial_kernel<T><<<grid, 256, 0, st>>>(fp, nx, nv, rows, part);
+  dim3 grid((unsigned)((nx + 63) / 64), (unsigned)o, (unsigned)nz);
+  density_partial_kernel<T><<<grid, 64 * kDensityWaves, 0, st>>>(fp, nx, nv, rows, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // int_{-1}^{0} P_j for j = 0..3
-  field_solve_kernel<<<1, kFieldThreads, 0, st>>>(part, nz, o, nx, hx, hv, dt, 1.0, -0.5, 0.0,
+  if (nx <= kFieldThreads)
+    field_solve_line_kernel<<<1, kFieldThreads, 0, st>>>(part, nz, o, nx, hx, hv, dt, 1.0, -0.5,
+                                                         0.0, 0.125, shift_out, field_out);
+  else
+    field_solve_kernel<<<1, kFieldThreads, 0, st>>>(part, nz, o, nx, hx, hv, dt, 1.0, -0.5, 0.0,
                                                   0.125, r, faces, shift_out, field_out);
   return hipGetLastError();
 }
@@ -181,14 +262,15 @@ __global__ __launch_bounds__(256) void density2_partial_kernel(const void* plane
   part[z * nxx + i] = acc;
 }
 
-__global__ __launch_bounds__(256) void density2_final_kernel(const double* __restrict__ part,
-                                                             int32_t nz, int64_t nxx,
-                                                             double hvv, double* __restrict__ rho) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nxx) return;
-  double acc = 0.0;
-  for (int32_t z = 0; z < nz; ++z) acc += part[(int64_t)z * nxx + i];
-  rho[i] = hvv * acc;
+// (One thread per x cell walked the up to 256 chunks in a chain of loads: 63 us
+// on a 36 x 32 x-grid, 3 us with the chunks over 16 waves.)
+__global__ __launch_bounds__(64 * kDensityWaves) void density2_final_kernel(
+    const double* __restrict__ part, int32_t nz, int64_t nxx, double hvv,
+    double* __restrict__ rho) {
+  __shared__ double sh[64 * kDensityWaves];
+  const int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+  const double s = column_sum(part, nxx, 0, nz, i, i < nxx, sh);
+  if (threadIdx.x < 64 && i < nxx) rho[i] = hvv * s;
 }
 
 // tw[r] = exp(2 pi i r / n), r < n, filled by the workgroup.
@@ -213,6 +295,7 @@ __global__ __launch_bounds__(256) void dft_x1_kernel(const double* __restrict__ 
   const double* row = rho + (int64_t)i2 * n1;
   double re = 0.0, im = 0.0;
   int32_t r = 0;
+#pragma unroll 4
   for (int32_t i1 = 0; i1 < n1; ++i1) {
     const double v = row[i1];
     re = fma(v, tw[r].x, re);
@@ -253,6 +336,7 @@ __global__ __launch_bounds__(256) void dft_x2_solve_kernel(const double2* __rest
   const int32_t k1 = (int32_t)(t % n1), k2 = (int32_t)(t / n1);
   double re = 0.0, im = 0.0;
   int32_t r = 0;
+#pragma unroll 4
   for (int32_t i2 = 0; i2 < n2; ++i2) {
     const double2 c = C[k1 + (int64_t)n1 * i2];
     const double2 w = tw[r];                       // exp(+...); the forward uses its conjugate
@@ -289,6 +373,7 @@ __global__ __launch_bounds__(256) void idft_x2_kernel(const double2* __restrict_
   const int32_t k1 = (int32_t)(t % n1), i2 = (int32_t)(t / n1);
   double a_re = 0.0, a_im = 0.0, b_re = 0.0, b_im = 0.0;
   int32_t r = 0;
+#pragma unroll 4
   for (int32_t k2 = 0; k2 < n2; ++k2) {
     const double2 w = tw[r];
     const double2 a = E1h[k1 + (int64_t)n1 * k2], b = E2h[k1 + (int64_t)n1 * k2];
@@ -320,6 +405,7 @@ __global__ __launch_bounds__(256) void idft_x1_kernel(const double2* __restrict_
   const double2* d2 = D2 + (int64_t)i2 * n1;
   double e1 = 0.0, e2 = 0.0;
   int32_t r = 0;
+#pragma unroll 4
   for (int32_t k1 = 0; k1 < n1; ++k1) {
     const double2 w = tw[r];
     e1 = fma(d1[k1].x, w.x, fma(-d1[k1].y, w.y, e1));
@@ -384,7 +470,7 @@ hipError_t launch_field2(int tier, const Field2Args& a, double* scratch, hipStre
   }
   if (e != hipSuccess) return e;
   const unsigned g = (unsigned)((nxx + 255) / 256);
-  density2_final_kernel<<<g, 256, 0, st>>>(part, nz, nxx, a.hv1 * a.hv2, rho);
+  density2_final_kernel<<<(unsigned)((nxx + 63) / 64), 64 * kDensityWaves, 0, st>>>(part, nz, nxx, a.hv1 * a.hv2, rho);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const size_t lds1 = sizeof(double2) * a.n1, lds2 = sizeof(double2) * a.n2;
   dft_x1_kernel<<<g, 256, lds1, st>>>(rho, a.n1, a.n2, C);

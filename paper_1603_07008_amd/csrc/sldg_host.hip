@@ -561,7 +561,10 @@ int32_t xy_tile_rows(const sldg_plan_s* p) {
     if (R > N1 && R > 1) continue;
     if (xy_lds_bytes(p->k, (int)elem_size(p->tier), (int32_t)N0, R) > kXYLdsBudget) continue;
     if ((int64_t)p->o * (R + 1) * (N0 / 4) > (int64_t)kXYMaxItems * 256) continue;
-    return R;
+    // the same number of tiles, of equal height (N1 = 32: two of 16 rows and
+    // not 24 + 8)
+    const int64_t chunks = (N1 + R - 1) / R;
+    return (int32_t)((N1 + chunks - 1) / chunks);
   }
   return 0;
 }
@@ -677,20 +680,21 @@ bool strang_eligible(const sldg_plan_s* p, StrangArgs& x, int64_t& nblocks) {
   return nblocks <= INT32_MAX;
 }
 
-// One X V X pass; the tables of the three sweeps are at entries pre[i] (nt[i]
-// entries each) of the plan's tables.
-sldg_status run_strang(sldg_plan_s* p, const uint32_t (&mask)[3], const int64_t (&pre)[3],
-                       const double* in_lo, const void* in_hi, double* out_lo, void* out_hi) {
+// One X V X pass (post 1), or V X X with one X table (post 2, the first entry
+// of mask and pre unused); the tables of the sweeps are at entries pre[i] of
+// the plan's tables, those along dimension 0 entry-major.
+sldg_status run_strang(sldg_plan_s* p, int post, const uint32_t (&mask)[3],
+                       const int64_t (&pre)[3], const double* in_lo, const void* in_hi,
+                       double* out_lo, void* out_hi) {
   StrangArgs x{};
   int64_t nblocks = 0;
   if (!strang_eligible(p, x, nblocks)) return fail(SLDG_ERR_UNSUPPORTED, "fused X V X sweeps");
-  const int64_t o2 = (int64_t)p->o * p->o;
+  const int64_t E = 2LL * p->o * p->o;
   LineTable* tab[3] = {&x.x0, &x.v, &x.x1};
-  for (int i = 0; i < 3; ++i) {
+  for (int i = post == 2 ? 1 : 0; i < 3; ++i) {
     SweepArgs a{};
     int64_t nt = 0;
     describe(p, i == 1 ? 1 : 0, mask[i], a, nt);
-    const int64_t E = 2 * o2;
     *tab[i] = {p->d_s + pre[i], p->d_ab + E * pre[i], i == 1 ? nt : 1, i == 1 ? 1 : E,
                (int32_t)(mask[i] >> (i == 1 ? 0 : 1) & 1), a.map};
   }
@@ -705,7 +709,7 @@ sldg_status run_strang(sldg_plan_s* p, const uint32_t (&mask)[3], const int64_t 
   x.fstrip = FastDiv::make((uint32_t)x.nstrip);
   x.ftile = FastDiv::make((uint32_t)x.ntile);
   x.fQ = FastDiv::make((uint32_t)x.Q);
-  const hipError_t e = launch_strang(p->k, (int)p->tier, 1, x, (int32_t)nblocks, p->stream);
+  const hipError_t e = launch_strang(p->k, (int)p->tier, post, x, (int32_t)nblocks, p->stream);
   if (e != hipSuccess) return device_error(e, "fused X V X launch");
   return SLDG_OK;
 }
@@ -1045,7 +1049,7 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
       } else if (fused[(size_t)q] == 3 && pre[(size_t)q] >= 0) {
         const uint32_t mask[3] = {seq[q].dep_mask, seq[q + 1].dep_mask, seq[q + 2].dep_mask};
         const int64_t at[3] = {pre[(size_t)q], pre[(size_t)q + 1], pre[(size_t)q + 2]};
-        st = run_strang(p, mask, at, m[cur], h[cur], m[1 - cur], h[1 - cur]);
+        st = run_strang(p, 1, mask, at, m[cur], h[cur], m[1 - cur], h[1 - cur]);
         q += 2;
       } else {
         st = run_sweep(p, seq[q].dim, seq[q].shift, seq[q].dep_mask, m[cur], h[cur], m[1 - cur],
@@ -1602,6 +1606,51 @@ sldg_status sldg_vlasov_poisson_steps(sldg_plan_t p, int nsteps, const double* s
         (p->hi_bytes > 0 && overlap(shift_v, ob, h[b], p->hi_bytes)))
       return fail(SLDG_ERR_ALIAS, "shift_v overlaps a state buffer");
   int cur = 0;
+  StrangArgs xs{};
+  int64_t nblocks = 0;
+  const int64_t N0 = p->n[0], N1 = p->n[1];
+  const int64_t second = N1;       // tables: the X table by entries, then the one in use
+  if (nsteps > 1 && strang_eligible(p, xs, nblocks) && N1 + std::max(N0, N1) <= p->table_cap) {
+    // The end of a step and the start of the next, V X X, are one pass; the
+    // first X and the last V and X run alone, so that the result lands in the
+    // buffer that three sweeps a step leave it in.  The X displacements are
+    // fixed over the call: their table is computed once.
+    const int64_t E = 2LL * p->o * p->o;
+    auto table = [&](int dim, const double* shift, bool by_entry) -> sldg_status {
+      const int64_t at = by_entry ? 0 : second;
+      const hipError_t e = launch_line_tables(p->k, dim ? N0 : N1, p->n[dim], shift, p->d_s + at,
+                                              p->d_ab + E * at, !by_entry, false, p->stream);
+      return e == hipSuccess ? SLDG_OK : device_error(e, "line-table launch");
+    };
+    auto sweep = [&](int dim, const double* shift, uint32_t mask) -> sldg_status {
+      sldg_status st = table(dim, shift, false);
+      if (st == SLDG_OK)
+        st = run_sweep(p, dim, shift, mask, m[cur], h[cur], m[1 - cur], h[1 - cur], false, nullptr,
+                       nullptr, second);
+      if (st == SLDG_OK) cur = 1 - cur;
+      return st;
+    };
+    const uint32_t mask[3] = {0, 1u, 2u};
+    const int64_t at[3] = {0, second, 0};
+    sldg_status st = table(0, shift_x, true);
+    if (st == SLDG_OK) st = sweep(0, shift_x, 2u);
+    for (int n = 0; n < nsteps && st == SLDG_OK; ++n) {
+      st = sldg_poisson_shift(p, m[cur], h[cur], hx, hv, dt, shift_v, nullptr);
+      if (st != SLDG_OK) break;
+      if (n + 1 < nsteps) {
+        st = table(1, shift_v, false);
+        if (st == SLDG_OK)
+          st = run_strang(p, 2, mask, at, m[cur], h[cur], m[1 - cur], h[1 - cur]);
+        cur = 1 - cur;
+      } else {
+        st = sweep(1, shift_v, 1u);
+        if (st == SLDG_OK) st = sweep(0, shift_x, 2u);
+      }
+    }
+    if (st != SLDG_OK) return st;
+    if (result_buffer) *result_buffer = cur;
+    return ok();
+  }
   for (int n = 0; n < nsteps; ++n) {
     // X(dt/2), field from the state, V(dt), X(dt/2)
     sldg_status st = run_sweep(p, 0, shift_x, 2u, m[cur], h[cur], m[1 - cur], h[1 - cur]);
@@ -1700,19 +1749,60 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
         return fail(SLDG_ERR_ALIAS, "a v shift table overlaps a state buffer");
   if (overlap(shift_v1, ob, shift_v2, ob)) return fail(SLDG_ERR_ALIAS, "shift_v1 overlaps shift_v2");
   int cur = 0;
+  // The x displacements are fixed over the call: their tables are computed
+  // once, before the steps, and those of the two v sweeps in one launch after
+  // each field solve, where all four fit the plan's table storage together.
+  const int64_t o2 = (int64_t)p->o * p->o;
+  const int64_t nx = p->n[2] + p->n[3], nv = p->n[0] * p->n[1];
+  const bool tables = nx + 2 * nv <= p->table_cap;
+  int64_t pre[4] = {-1, -1, -1, -1};
+  auto compute = [&](int d0, int64_t at) -> sldg_status {
+    TableSet set{};
+    set.count = 2;
+    for (int i = 0; i < 2; ++i) {
+      const int64_t n = d0 == 0 ? p->n[2 + i] : nv;
+      set.first[i + 1] = set.first[i] + n;
+      set.period[i] = p->n[d0 + i];
+      set.sigma[i] = sh[d0 + i];
+      pre[d0 + i] = at + set.first[i];
+    }
+    const hipError_t e =
+        launch_line_tables_set(p->k, set, p->d_s + at, p->d_ab + 2 * o2 * at, p->stream);
+    return e == hipSuccess ? SLDG_OK : device_error(e, "line-table launch");
+  };
   auto sweep = [&](int d) {
-    sldg_status st = run_sweep(p, d, sh[d], dep[d], m[cur], hh[cur], m[1 - cur], hh[1 - cur]);
+    sldg_status st = run_sweep(p, d, sh[d], dep[d], m[cur], hh[cur], m[1 - cur], hh[1 - cur], false,
+                               nullptr, nullptr, pre[d]);
     if (st == SLDG_OK) cur = 1 - cur;
     return st;
   };
+  // X1 X2 as one fused pass where it can run (two passes a step, as four
+  // sweeps, end in the buffer they started from)
+  const char* why = nullptr;
+  const bool pair =
+      p->fuse && xy_eligible(p, dep[0], dep[1], m[0], hh[0], m[1], hh[1], &why);
+  auto x_sweeps = [&] {
+    sldg_status st;
+    if (pair) {
+      st = run_xy(p, sh[0], dep[0], sh[1], dep[1], m[cur], hh[cur], m[1 - cur], hh[1 - cur], pre[0],
+                  pre[1]);
+      if (st == SLDG_OK) cur = 1 - cur;
+    } else {
+      st = sweep(0);
+      if (st == SLDG_OK) st = sweep(1);
+    }
+    return st;
+  };
+  sldg_status st = SLDG_OK;
+  if (tables && nsteps > 0 && (st = compute(0, 0)) != SLDG_OK) return st;
   for (int n = 0; n < nsteps; ++n) {
     // X1(dt/2) X2(dt/2), the field of the state, V1(dt) V2(dt), X1(dt/2) X2(dt/2)
-    sldg_status st;
-    if ((st = sweep(0)) != SLDG_OK || (st = sweep(1)) != SLDG_OK) return st;
+    if ((st = x_sweeps()) != SLDG_OK) return st;
     st = sldg_poisson_shift_2d(p, m[cur], hh[cur], h, dt, shift_v1, shift_v2, nullptr);
+    if (st == SLDG_OK && tables) st = compute(2, nx);
     if (st != SLDG_OK) return st;
     if ((st = sweep(2)) != SLDG_OK || (st = sweep(3)) != SLDG_OK) return st;
-    if ((st = sweep(0)) != SLDG_OK || (st = sweep(1)) != SLDG_OK) return st;
+    if ((st = x_sweeps()) != SLDG_OK) return st;
   }
   if (result_buffer) *result_buffer = cur;
   return ok();

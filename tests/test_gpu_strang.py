@@ -163,3 +163,52 @@ def test_batched_passes(sl, tier):
                     assert torch.equal(_bits(got), _bits(ref)), (ns, k, graph)
                 plan.close()
         b.close()
+
+
+@pytest.mark.parametrize("ns,k,tier", [((40, 90), 1, "fp32"), ((130, 33), 2, "bf16"),
+                                       ((63, 63), 3, "fp64"), ((1100, 20), 1, "fp16")])
+def test_self_consistent_steps(sl, ns, k, tier):
+    """Vlasov-Poisson steps (V X X passes between field solves) are bitwise the
+    sweeps and field solves one by one; N_x above and below the threads of the
+    field solve."""
+    import torch
+    hx, hv, dt = 0.3, 0.2, 0.1
+    plan = sl.Plan(ns, k, tier)
+    st = _state(plan, 6)
+    sx = _seq(ns, 2, 1, 4.0, 0.3, 8)[0][2]
+    for nsteps in (1, 2, 5):
+        a = tuple(t.clone() for t in st)
+        b = plan.empty_state()
+        got = (a, b)[plan.vlasov_poisson_steps(nsteps, sx, hx, hv, dt, a, b)]
+        buf = [tuple(t.clone() for t in st), plan.empty_state()]
+        cur = 0
+        for _ in range(nsteps):
+            for dim in (0, 1, 0):
+                mask, s = (2, sx) if dim == 0 else (1, plan.poisson_shift(*buf[cur], hx, hv, dt))
+                plan.advect_dim(dim, s, mask, *buf[cur], *buf[1 - cur])
+                cur = 1 - cur
+        torch.cuda.synchronize()
+        for x, y in zip(got, buf[cur]):
+            assert torch.equal(_bits(x), _bits(y)), nsteps
+    plan.close()
+
+
+@pytest.mark.parametrize("ns", [(12, 9, 5, 7), (9, 6, 4, 5), (8, 8, 1, 1)])
+def test_self_consistent_steps_2d2v(sl, ns):
+    """2D-2V Vlasov-Poisson steps with the (x1, x2) sweeps fused (and where they
+    cannot be, or the tables do not fit together) are bitwise the unfused ones."""
+    import torch
+    plan = sl.Plan(ns, 2, "fp32")
+    st = _state(plan, 2)
+    seq = [torch.linspace(-2.0, 2.0, ns[d], dtype=torch.float64, device="cuda") for d in (2, 3)]
+    out = []
+    for fuse in (False, True):
+        plan.set_fusion(fuse)
+        a = tuple(t.clone() for t in st)
+        b = plan.empty_state()
+        r = plan.vlasov_poisson_steps_2d2v(2, *seq, (0.3, 0.4, 0.2, 0.25), 0.1, a, b)
+        out.append((a, b)[r])
+    torch.cuda.synchronize()
+    for x, y in zip(*out):
+        assert torch.equal(_bits(x), _bits(y))
+    plan.close()
