@@ -168,9 +168,14 @@ typedef struct {
  * result is bitwise the same, but the pair then takes one pass instead of
  * two.  Other sweeps along 0, 1, 0 in a row (a Strang step X V X of an (x, v)
  * problem) run as one pass too, bitwise the three sweeps, where at most the
- * cell mean is FP64 and kernel timing (sldg_timing_enable) is off.
+ * cell mean is FP64 and kernel timing (sldg_timing_enable) is off.  A sweep
+ * along d >= 1 directly followed by one along d + 1, both with displacements of
+ * the dimensions below d alone (v1 and v2 moved by E(x1, x2)), runs as one pass
+ * too, bitwise the two, where at most the cell mean is FP64 and the dimensions
+ * below d give it enough columns.
  * *result_buffer receives the buffer (0 or 1) holding the result:
- * (nsteps * nseq) % 2 without fused pairs.
+ * (nsteps * nseq) % 2 without fused pairs.  With result_buffer NULL pairs along
+ * higher dimensions do not change that buffer.
  * Buffers 0 and 1 must not overlap.  Asynchronous on the plan's stream.
  */
 sldg_status sldg_split_steps(sldg_plan_t plan, const sldg_sweep_desc* seq, int nseq,
@@ -482,7 +487,8 @@ sldg_status sldg_poisson_shift_2d(sldg_plan_t plan, const double* mass, const vo
  *   - V1(dt), V2(dt);
  *   - X1(dt/2), X2(dt/2).
  * Buffers as in sldg_split_steps.  *result_buffer receives the buffer holding
- * the result.  Asynchronous on the plan's stream.
+ * the result (with result_buffer NULL it is buffer 0).  Passes are fused as
+ * there.  Asynchronous on the plan's stream.
  */
 sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t plan, int nsteps, const double* shift_x1,
                                            const double* shift_x2, const double* h, double dt,
@@ -497,7 +503,8 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t plan, int nsteps, const d
  * sldg_timing_enable(plan, 1) clears earlier records; (plan, 0) stops.
  * sldg_timing_read synchronises the plan's stream and returns, for launches
  * of the sweep along `dim` (dim = -1: along dimension 0; dim = -2: along
- * any dimension > 0; dim = -3: the fused (0, 1) passes), their count and the
+ * any dimension > 0, fused pairs along two of them as one launch; dim = -3: the
+ * fused (0, 1) passes), their count and the
  * sum of their durations in ms.
  */
 sldg_status sldg_timing_enable(sldg_plan_t plan, int enable);

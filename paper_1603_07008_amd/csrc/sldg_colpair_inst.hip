@@ -1,0 +1,20 @@
+// Instantiation unit of the fused column pair (sldg_colpair.h) for one degree k
+// and one storage tier, selected when compiling (-DSLDG_K=1..3
+// -DSLDG_TIER=0..3) as sldg_sweep_inst.hip is.
+#include "sldg_colpair.h"
+
+#if !defined(SLDG_K) || !defined(SLDG_TIER)
+#error "compile with -DSLDG_K=<degree> -DSLDG_TIER=<tier>"
+#endif
+
+namespace sldg {
+
+template <int K, int TIER>
+hipError_t launch_colpair_inst(const ColPairArgs& a, int32_t nblocks, hipStream_t st) {
+  sweep_colpair_kernel<K, TIER><<<nblocks, 256, 0, st>>>(a);
+  return hipGetLastError();
+}
+
+template hipError_t launch_colpair_inst<SLDG_K, SLDG_TIER>(const ColPairArgs&, int32_t, hipStream_t);
+
+}  // namespace sldg

@@ -22,6 +22,7 @@
 #include "sldg_colloc.h"
 #include "sldg_fused.h"
 #include "sldg_strang.h"
+#include "sldg_colpair.h"
 
 using namespace sldg;
 
@@ -257,6 +258,7 @@ namespace {
 
 constexpr int kMaxTimed = 4096;
 constexpr int kXYTimingDim = -3;   // timing code of the fused (0, 1) pair
+constexpr int kPairTimingDim = 1 << 16;   // ... of the fused pairs along higher ones: of no single one
 
 sldg_status check_sweep(const sldg_plan_s* p, int dim, const double* shift, uint32_t dep_mask,
                         const double* in_lo, const void* in_hi, const double* out_lo,
@@ -714,6 +716,93 @@ sldg_status run_strang(sldg_plan_s* p, int post, const uint32_t (&mask)[3],
   return SLDG_OK;
 }
 
+// Workgroups below which a column pair takes shorter strips (16^4 cells, k = 2,
+// FP32: 23 us at 6 rows a strip, 33 us at 16).
+constexpr int64_t kPairBlocks = 512;
+
+// Whether the sweeps along d >= 1 and d + 1 can run as one pass
+// (sldg_colpair.h): displacements of the dimensions below d alone, at most the
+// cell mean FP64, a plane within 31-bit byte offsets and a launchable grid; and
+// whether it pays.  That takes three quarters of the lanes (columns below d
+// over a whole number of waves: 48 of 64 columns x 160^2, k = 2, bf16: 65 us
+// against 74 for the two sweeps; 40 columns 62 against 57, 16 columns 61 against
+// 26), and four rows of d + 1 (a strip reads three more than it writes; 8192
+// columns x 64 x 4 rows 270 us against 316, x 2 rows 207 against 172).  For
+// k = 3 eight rows and seven eighths of the lanes: its waves hold one row of d
+// and read three (12^4 cells, 144 columns in 192 lanes, FP64: 50 us against 36;
+// 16^4 79 against 127).
+// Sets everything but the buffers and tables.
+bool colpair_eligible(const sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask2, ColPairArgs& x,
+                      int64_t& nblocks) {
+  if (!p->fuse || d < 1 || d + 1 >= p->ndim || ((mask1 | mask2) >> d) || p->n_lo > 1) return false;
+  if (p->cells * 8 > (int64_t)INT32_MAX) return false;
+  int64_t P = 1, ms = 1;
+  for (int e = 0; e < d; ++e) {
+    P *= p->n[e];
+    ms *= p->o;
+  }
+  x.P = (int32_t)P;
+  x.N1 = (int32_t)p->n[d];
+  x.N2 = (int32_t)p->n[d + 1];
+  x.Q = (int32_t)(p->cells / (P * p->n[d] * p->n[d + 1]));
+  x.ms = (int32_t)ms;
+  const int64_t groups = p->modes / (p->o * p->o);
+  x.nblk = (int32_t)((P + 63) / 64);
+  const bool high = p->k == 3;
+  if (x.N1 < 2 || x.N2 < (high ? 8 : 4) || P * 8 < (high ? 7 : 6) * 64LL * x.nblk) return false;
+  const int32_t L = colpair_rows(p->k, (int)p->tier);
+  x.nchunk = (x.N1 + 4 * L - 1) / (4 * L);
+  nblocks = (int64_t)x.nchunk * x.nblk * x.Q * groups;
+  // Rows of d + 1 per wave (48^4: k = 2 FP32 728 us at 24, 749 at 48; bf16 448
+  // and 433; k = 1 FP32 154 and 165).
+  const int64_t most = p->k > 1 && (p->tier == SLDG_TIER_BF16 || p->tier == SLDG_TIER_FP16) ? 48 : 24;
+  const int64_t fill = x.N2 * nblocks / kPairBlocks;
+  const int64_t rows = std::min(most, std::max<int64_t>(fill, 6));
+  const int64_t ns = (x.N2 + rows - 1) / rows;
+  x.R = (int32_t)((x.N2 + ns - 1) / ns);
+  x.nstrip = (x.N2 + x.R - 1) / x.R;
+  nblocks *= x.nstrip;
+  return nblocks <= INT32_MAX;
+}
+
+// The fused pair along d and d + 1; its tables are at entries pre1 and pre2 of
+// the plan's tables.
+sldg_status run_colpair(sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask2, int64_t pre1,
+                        int64_t pre2, const double* in_lo, const void* in_hi, double* out_lo,
+                        void* out_hi) {
+  ColPairArgs x{};
+  int64_t nblocks = 0;
+  if (!colpair_eligible(p, d, mask1, mask2, x, nblocks))
+    return fail(SLDG_ERR_UNSUPPORTED, "fused sweeps along dimensions %d and %d", d, d + 1);
+  const int64_t E = 2LL * p->o * p->o;
+  SweepArgs a1{}, a2{};
+  describe(p, d, mask1, a1, x.cs1);
+  describe(p, d + 1, mask2, a2, x.cs2);
+  x.map1 = a1.map;
+  x.map2 = a2.map;
+  x.s1 = p->d_s + pre1;
+  x.ab1 = p->d_ab + E * pre1;
+  x.s2 = p->d_s + pre2;
+  x.ab2 = p->d_ab + E * pre2;
+  x.in_lo = in_lo;
+  x.in_hi = in_hi;
+  x.out_lo = out_lo;
+  x.out_hi = out_hi;
+  x.n_lo = (int32_t)p->n_lo;
+  x.cells = p->cells;
+  x.one = 1.0f;
+  x.fblk = FastDiv::make((uint32_t)x.nblk);
+  x.fstrip = FastDiv::make((uint32_t)x.nstrip);
+  x.fchunk = FastDiv::make((uint32_t)x.nchunk);
+  x.fQ = FastDiv::make((uint32_t)x.Q);
+  bool timed = false;
+  const sldg_status tst = timing_begin(p, timed);
+  if (tst != SLDG_OK) return tst;
+  const hipError_t e = launch_colpair(p->k, (int)p->tier, x, (int32_t)nblocks, p->stream);
+  if (e != hipSuccess) return device_error(e, "fused sweep launch");
+  return timing_end(p, timed, kPairTimingDim);
+}
+
 }  // namespace
 
 extern "C" {
@@ -984,12 +1073,24 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
   // (same result, one read and one write of the state instead of two); the
   // pair's result then lands in the other buffer than two sweeps would leave
   // it in, which *result_buffer reports.  Elsewhere sweeps along 0, 1, 0 run
-  // as one pass (three sweeps and one pass end in the same buffer).
+  // as one pass (three sweeps and one pass end in the same buffer).  Sweeps
+  // along d >= 1 then d + 1 run as one where that pays; a caller that does not
+  // ask for the result's buffer finds it where (0, 1) pairs alone leave it: the
+  // last step then runs one such pair as two sweeps if need be.
+  int pairs = 0;
   std::vector<char> fused((size_t)std::max(nseq, 1), 0);
   for (int q = 0; p->fuse && q + 1 < nseq; ++q) {
     const char* why = nullptr;
     StrangArgs x{};
     int64_t nblocks = 0;
+    ColPairArgs cp{};
+    if (seq[q].dim > 0 && seq[q + 1].dim == seq[q].dim + 1 &&
+        colpair_eligible(p, seq[q].dim, seq[q].dep_mask, seq[q + 1].dep_mask, cp, nblocks)) {
+      fused[(size_t)q] = 4;
+      ++pairs;
+      ++q;
+      continue;
+    }
     if (seq[q].dim != 0 || seq[q + 1].dim != 1) continue;
     if (!adjoint &&
         xy_eligible(p, seq[q].dep_mask, seq[q + 1].dep_mask, m[0], h[0], m[1], h[1], &why)) {
@@ -1039,9 +1140,14 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
     }
   }
   int cur = 0;
+  bool split = !result_buffer && (int64_t)pairs * nsteps % 2;
   for (int n = 0; n < nsteps; ++n) {
     for (int q = 0; q < nseq; ++q) {
       sldg_status st;
+      if (split && n + 1 == nsteps && fused[(size_t)q] == 4) {
+        fused[(size_t)q] = 0;
+        split = false;
+      }
       if (fused[(size_t)q] == 2) {
         st = run_xy(p, seq[q].shift, seq[q].dep_mask, seq[q + 1].shift, seq[q + 1].dep_mask,
                     m[cur], h[cur], m[1 - cur], h[1 - cur], pre[(size_t)q], pre[(size_t)q + 1]);
@@ -1051,6 +1157,10 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
         const int64_t at[3] = {pre[(size_t)q], pre[(size_t)q + 1], pre[(size_t)q + 2]};
         st = run_strang(p, 1, mask, at, m[cur], h[cur], m[1 - cur], h[1 - cur]);
         q += 2;
+      } else if (fused[(size_t)q] == 4 && pre[(size_t)q] >= 0) {
+        st = run_colpair(p, seq[q].dim, seq[q].dep_mask, seq[q + 1].dep_mask, pre[(size_t)q],
+                         pre[(size_t)q + 1], m[cur], h[cur], m[1 - cur], h[1 - cur]);
+        ++q;
       } else {
         st = run_sweep(p, seq[q].dim, seq[q].shift, seq[q].dep_mask, m[cur], h[cur], m[1 - cur],
                        h[1 - cur], adjoint, nullptr, nullptr, pre[(size_t)q]);
@@ -1777,10 +1887,15 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
     return st;
   };
   // X1 X2 as one fused pass where it can run (two passes a step, as four
-  // sweeps, end in the buffer they started from)
+  // sweeps, end in the buffer they started from), and V1 V2 (one pass a step: a
+  // caller that does not ask for the result's buffer finds it in buffer 0, the
+  // last of an odd number of steps running the two sweeps)
   const char* why = nullptr;
   const bool pair =
       p->fuse && xy_eligible(p, dep[0], dep[1], m[0], hh[0], m[1], hh[1], &why);
+  ColPairArgs cp{};
+  int64_t nblocks = 0;
+  const bool vpair = tables && colpair_eligible(p, 2, dep[2], dep[3], cp, nblocks);
   auto x_sweeps = [&] {
     sldg_status st;
     if (pair) {
@@ -1793,6 +1908,18 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
     }
     return st;
   };
+  auto v_sweeps = [&](bool last) {
+    sldg_status st;
+    if (vpair && !(last && !result_buffer && nsteps % 2)) {
+      st = run_colpair(p, 2, dep[2], dep[3], pre[2], pre[3], m[cur], hh[cur], m[1 - cur],
+                       hh[1 - cur]);
+      if (st == SLDG_OK) cur = 1 - cur;
+    } else {
+      st = sweep(2);
+      if (st == SLDG_OK) st = sweep(3);
+    }
+    return st;
+  };
   sldg_status st = SLDG_OK;
   if (tables && nsteps > 0 && (st = compute(0, 0)) != SLDG_OK) return st;
   for (int n = 0; n < nsteps; ++n) {
@@ -1801,7 +1928,7 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
     st = sldg_poisson_shift_2d(p, m[cur], hh[cur], h, dt, shift_v1, shift_v2, nullptr);
     if (st == SLDG_OK && tables) st = compute(2, nx);
     if (st != SLDG_OK) return st;
-    if ((st = sweep(2)) != SLDG_OK || (st = sweep(3)) != SLDG_OK) return st;
+    if ((st = v_sweeps(n + 1 == nsteps)) != SLDG_OK) return st;
     if ((st = x_sweeps()) != SLDG_OK) return st;
   }
   if (result_buffer) *result_buffer = cur;

@@ -185,6 +185,12 @@ hipError_t launch_strang_inst(int post, const StrangArgs& a, int32_t nblocks, hi
 template <int K, int TIER>
 hipError_t launch_batch_strang_inst(const StrangArgs* args, const BatchItem* items, int32_t nitems,
                                     int32_t xcd, hipStream_t st);
+// The fused pair of sweeps along d >= 1 and d + 1 (sldg_colpair.h): nblocks
+// workgroups of four waves.
+struct ColPairArgs;
+hipError_t launch_colpair(int k, int tier, const ColPairArgs& a, int32_t nblocks, hipStream_t st);
+template <int K, int TIER>
+hipError_t launch_colpair_inst(const ColPairArgs& a, int32_t nblocks, hipStream_t st);
 // Waves of one sweep launch that compute a given output plane (the absmax
 // partial slots per plane of a scaled FP16 sweep).
 int64_t sweep_slots(int dim, const SweepArgs& a);

@@ -394,6 +394,38 @@ hipError_t launch_batch_strang(int k, int tier, const StrangArgs* args, const Ba
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_colpair(int k, int tier, const ColPairArgs& a, int32_t nblocks, hipStream_t st) {
+#define SLDG_PAIR_CALL(KK, TT) launch_colpair_inst<KK, TT>(a, nblocks, st)
+  switch (k) {
+    case 1:
+      switch (tier) {
+        case 0: return SLDG_PAIR_CALL(1, 0);
+        case 1: return SLDG_PAIR_CALL(1, 1);
+        case 2: return SLDG_PAIR_CALL(1, 2);
+        case 3: return SLDG_PAIR_CALL(1, 3);
+      }
+      break;
+    case 2:
+      switch (tier) {
+        case 0: return SLDG_PAIR_CALL(2, 0);
+        case 1: return SLDG_PAIR_CALL(2, 1);
+        case 2: return SLDG_PAIR_CALL(2, 2);
+        case 3: return SLDG_PAIR_CALL(2, 3);
+      }
+      break;
+    case 3:
+      switch (tier) {
+        case 0: return SLDG_PAIR_CALL(3, 0);
+        case 1: return SLDG_PAIR_CALL(3, 1);
+        case 2: return SLDG_PAIR_CALL(3, 2);
+        case 3: return SLDG_PAIR_CALL(3, 3);
+      }
+      break;
+  }
+#undef SLDG_PAIR_CALL
+  return hipErrorInvalidValue;
+}
+
 // ---------------------------------------------------------------------------
 // Batched sweep: many independent problems (own grid, degree and tables).
 // The work list of a sweep holds one item per workgroup-sized tile of one
