@@ -172,7 +172,9 @@ typedef struct {
  * along d >= 1 directly followed by one along d + 1, both with displacements of
  * the dimensions below d alone (v1 and v2 moved by E(x1, x2)), runs as one pass
  * too, bitwise the two, where at most the cell mean is FP64 and the dimensions
- * below d give it enough columns.
+ * below d give it enough columns.  The sweeps of a 1D plan of up to 4096 cells
+ * run many to a launch, bitwise the same and into the same buffer, where its
+ * line fits LDS, at most the cell mean is FP64 and kernel timing is off.
  * *result_buffer receives the buffer (0 or 1) holding the result:
  * (nsteps * nseq) % 2 without fused pairs.  With result_buffer NULL pairs along
  * higher dimensions do not change that buffer.

@@ -17,13 +17,15 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsldg.so")
 PLAIN = ["sldg_host.hip", "sldg_batch.hip", "sldg_kernels.hip", "sldg_ref.hip", "sldg_field.hip",
          "sldg_colloc.hip"]
-INST = ["sldg_sweep_inst.hip", "sldg_strang_inst.hip", "sldg_colpair_inst.hip"]
+INST = ["sldg_sweep_inst.hip", "sldg_strang_inst.hip", "sldg_colpair_inst.hip",
+        "sldg_line_inst.hip"]
 DEGREES = (1, 2, 3)
 TIERS = (0, 1, 2, 3)
 SOURCES = [os.path.join(CSRC, f) for f in PLAIN + INST]
 HEADERS = [os.path.join(CSRC, f) for f in ("sldg_internal.h", "sldg_sweep.h", "ab_poly.h",
                                           "sldg_ref.h", "sldg_field.h", "sldg_colloc.h",
-                                          "sldg_fused.h", "sldg_staged.h", "sldg_strang.h", "sldg_colpair.h")] + \
+                                          "sldg_fused.h", "sldg_staged.h", "sldg_strang.h",
+                                          "sldg_colpair.h", "sldg_line.h")] + \
     [os.path.join(ROOT, "include", "sldg.h")]
 ARCH = os.environ.get("SLDG_OFFLOAD_ARCH", "gfx950")
 

@@ -23,6 +23,7 @@
 #include "sldg_fused.h"
 #include "sldg_strang.h"
 #include "sldg_colpair.h"
+#include "sldg_line.h"
 
 using namespace sldg;
 
@@ -803,6 +804,54 @@ sldg_status run_colpair(sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask2, i
   return timing_end(p, timed, kPairTimingDim);
 }
 
+constexpr int32_t kLineLds = 160 * 1024;      // LDS of a compute unit
+constexpr int64_t kLineSweeps = 1 << 14;      // sweeps of one launch (some 50 ms at most)
+
+// Whether split steps of a 1D problem can run as launches of many sweeps
+// (sldg_line.h): the line fits the LDS and 1024 lanes of four cells, at most
+// the cell mean FP64, no timing of single sweeps.  Faster over the whole range:
+// 300 sweeps, k = 2, FP64, of 16 cells 61 us against 1132 sweep by sweep, 4096
+// cells 402 against 1264.
+bool line_steps_eligible(const sldg_plan_s* p) {
+  return p->fuse && !p->timing && p->ndim == 1 && p->n_lo <= 1 && p->n[0] <= 4096 &&
+         p->n[0] * line_cell_bytes(p->o, p->n_lo, elem_size(p->tier)) <= kLineLds;
+}
+
+// `total` sweeps of the sequence whose tables are at entries pre[q] of the
+// plan's tables, from buffer cur on; cur becomes the buffer of the result.
+sldg_status run_line_steps(sldg_plan_s* p, const std::vector<int64_t>& pre, int nseq, int64_t total,
+                           double* const (&m)[2], void* const (&h)[2], int& cur) {
+  LineStepsArgs x{};
+  x.n_lo = (int32_t)p->n_lo;
+  x.N = (int32_t)p->n[0];
+  x.nseq = nseq;
+  x.one = 1.0f;
+  x.s = p->d_s;
+  x.ab = p->d_ab;
+  for (int q = 0; q < nseq; ++q) x.pre[q] = (int32_t)pre[(size_t)q];
+  const int32_t bytes =
+      (int32_t)((x.N * line_cell_bytes(p->o, p->n_lo, elem_size(p->tier)) + 15) & ~15LL);
+  x.stride = 2 * bytes <= kLineLds ? bytes : 0;
+  // as many lanes as a workgroup holds: fewer lanes of more cells take longer
+  // (256 cells, k = 2, FP64, 300 sweeps: 85, 109, 161 us at 1, 2, 4 cells a lane)
+  const int cells = x.N <= 1024 ? 1 : x.N <= 2048 ? 2 : 4;
+  // each launch starts at the first sweep of the sequence
+  const int64_t most = std::max<int64_t>(kLineSweeps / nseq, 1) * nseq;
+  for (int64_t done = 0; done < total; done += x.sweeps) {
+    x.sweeps = (int32_t)std::min(most, total - done);
+    const int to = cur ^ (x.sweeps & 1);
+    x.in_lo = m[cur];
+    x.in_hi = h[cur];
+    x.out_lo = m[to];
+    x.out_hi = h[to];
+    const hipError_t e = launch_line_steps(p->k, (int)p->tier, x, cells,
+                                           x.stride ? 2 * x.stride : bytes, p->stream);
+    if (e != hipSuccess) return device_error(e, "1D steps launch");
+    cur = to;
+  }
+  return SLDG_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1140,6 +1189,12 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
     }
   }
   int cur = 0;
+  if (pre[0] >= 0 && (int64_t)nseq * nsteps > 1 && line_steps_eligible(p)) {
+    const sldg_status st = run_line_steps(p, pre, nseq, (int64_t)nseq * nsteps, m, h, cur);
+    if (st != SLDG_OK) return st;
+    if (result_buffer) *result_buffer = cur;
+    return ok();
+  }
   bool split = !result_buffer && (int64_t)pairs * nsteps % 2;
   for (int n = 0; n < nsteps; ++n) {
     for (int q = 0; q < nseq; ++q) {

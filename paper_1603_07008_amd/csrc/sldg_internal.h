@@ -191,6 +191,13 @@ struct ColPairArgs;
 hipError_t launch_colpair(int k, int tier, const ColPairArgs& a, int32_t nblocks, hipStream_t st);
 template <int K, int TIER>
 hipError_t launch_colpair_inst(const ColPairArgs& a, int32_t nblocks, hipStream_t st);
+// Sweeps of a 1D problem in one launch (sldg_line.h): one workgroup of `cells`
+// (1, 2, 4) cells a lane, lds bytes of LDS.
+struct LineStepsArgs;
+hipError_t launch_line_steps(int k, int tier, const LineStepsArgs& a, int cells, int32_t lds,
+                             hipStream_t st);
+template <int K, int TIER>
+hipError_t launch_line_steps_inst(const LineStepsArgs& a, int cells, int32_t lds, hipStream_t st);
 // Waves of one sweep launch that compute a given output plane (the absmax
 // partial slots per plane of a scaled FP16 sweep).
 int64_t sweep_slots(int dim, const SweepArgs& a);

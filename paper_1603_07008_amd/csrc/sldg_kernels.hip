@@ -426,6 +426,39 @@ hipError_t launch_colpair(int k, int tier, const ColPairArgs& a, int32_t nblocks
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_line_steps(int k, int tier, const LineStepsArgs& a, int cells, int32_t lds,
+                             hipStream_t st) {
+#define SLDG_LINE_CALL(KK, TT) launch_line_steps_inst<KK, TT>(a, cells, lds, st)
+  switch (k) {
+    case 1:
+      switch (tier) {
+        case 0: return SLDG_LINE_CALL(1, 0);
+        case 1: return SLDG_LINE_CALL(1, 1);
+        case 2: return SLDG_LINE_CALL(1, 2);
+        case 3: return SLDG_LINE_CALL(1, 3);
+      }
+      break;
+    case 2:
+      switch (tier) {
+        case 0: return SLDG_LINE_CALL(2, 0);
+        case 1: return SLDG_LINE_CALL(2, 1);
+        case 2: return SLDG_LINE_CALL(2, 2);
+        case 3: return SLDG_LINE_CALL(2, 3);
+      }
+      break;
+    case 3:
+      switch (tier) {
+        case 0: return SLDG_LINE_CALL(3, 0);
+        case 1: return SLDG_LINE_CALL(3, 1);
+        case 2: return SLDG_LINE_CALL(3, 2);
+        case 3: return SLDG_LINE_CALL(3, 3);
+      }
+      break;
+  }
+#undef SLDG_LINE_CALL
+  return hipErrorInvalidValue;
+}
+
 // ---------------------------------------------------------------------------
 // Batched sweep: many independent problems (own grid, degree and tables).
 // The work list of a sweep holds one item per workgroup-sized tile of one
