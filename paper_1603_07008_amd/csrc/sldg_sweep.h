@@ -271,6 +271,45 @@ __device__ __forceinline__ float wave_max(float v) {
   return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
 }
 
+// The maxima over the wave (every lane active) of am[ND .. K], that of am[l] in
+// lane l - ND: the planes are reduced together, the first exchanges halving the
+// values a lane carries (lane ^ 1: planes 0 and 1, 2 and 3; lane ^ 2: the two
+// pairs), the rest over the rows of 16 and across them.  15 vector instructions
+// for three planes, where one wave_max per plane takes 33 with the selection of
+// the lane's.
+template <int K, int ND>
+__device__ __forceinline__ float wave_max_planes(const float (&am)[K + 1], int32_t lane) {
+  constexpr int NP = K + 1 - ND;
+  if constexpr (NP <= 0) {
+    return 0.0f;
+  } else {
+    auto v = [&](int i) { return i < NP ? am[ND + (i < NP ? i : 0)] : 0.0f; };
+    const bool odd = lane & 1, up = lane & 2;
+    auto meet = [&](float p0, float p1) {
+      return fmaxf(odd ? p1 : p0, dpp_f<0xB1>(odd ? p0 : p1));   // quad_perm [1, 0, 3, 2]
+    };
+    float m;
+    if constexpr (NP == 1) m = fmaxf(v(0), dpp_f<0xB1>(v(0)));
+    else m = meet(v(0), v(1));
+    if constexpr (NP <= 2) {
+      m = fmaxf(m, dpp_f<0x4E>(m));                              // quad_perm [2, 3, 0, 1]
+    } else {
+      const float n = meet(v(2), v(3));
+      m = fmaxf(up ? n : m, dpp_f<0x4E>(up ? m : n));
+    }
+    m = fmaxf(m, dpp_f<0x124>(m));                               // row_ror 4
+    m = fmaxf(m, dpp_f<0x128>(m));                               // row_ror 8
+    // Odd rows of one copy exchanged with even rows of the other, then the halves
+    // of the wave.  In asm: the builtins' two results of equal operands are taken
+    // for equal.
+    float w = m;
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(m), "+v"(w));
+    m = w = fmaxf(m, w);
+    asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(m), "+v"(w));
+    return fmaxf(m, w);
+  }
+}
+
 // Stored value -> register value (the FP16 tier widens and unscales).
 template <int TIER, class T>
 __device__ __forceinline__ typename Tier<TIER>::R to_reg(T v, float fin) {
@@ -385,15 +424,11 @@ __device__ __forceinline__ void flush_amax(const SweepArgs& a, const Planes<K, T
         a.amax_part, (short)0, on ? 0x7fffffff : 0, 0x00020000);
     const int32_t lane = (int32_t)(threadIdx.x & 63);
     float mv = 0.0f;
+    if (on) mv = wave_max_planes<K, ND>(am, lane);
     int32_t off = 0x7fffffff;                  // past the buffer: no write
 #pragma unroll
-    for (int l = ND; l < K + 1; ++l) {
-      const float m = on ? wave_max(am[l]) : 0.0f;
-      if (lane == l - ND) {
-        mv = m;
-        off = (int32_t)(((int64_t)pl.hp[l] * a.nslot + slot) * 4);
-      }
-    }
+    for (int l = ND; l < K + 1; ++l)
+      if (lane == l - ND) off = (int32_t)(((int64_t)pl.hp[l] * a.nslot + slot) * 4);
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, mv), rs, off, 0, 0);
   }
 }
