@@ -34,7 +34,8 @@ ARITH = {"fp64": "f64", "fp32": "f64", "bf16": "f32", "fp16": "f32"}
 KERNEL_SOURCES = ["paper_1603_07008_amd/csrc/sldg_kernels.hip", "paper_1603_07008_amd/csrc/ab_poly.h",
                   "paper_1603_07008_amd/csrc/sldg_internal.h", "paper_1603_07008_amd/csrc/sldg_sweep.h",
                   "paper_1603_07008_amd/csrc/sldg_sweep_inst.hip", "paper_1603_07008_amd/csrc/sldg_fused.h",
-                  "paper_1603_07008_amd/csrc/sldg_staged.h"]
+                  "paper_1603_07008_amd/csrc/sldg_staged.h", "paper_1603_07008_amd/csrc/sldg_strang.h",
+                  "paper_1603_07008_amd/csrc/sldg_colpair.h"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_vlasov4d_48_k2.json")
 
 
@@ -153,8 +154,8 @@ def sweep_kernel_name(ns, k, tier, d, shape, form=None):
 
 def run_tier(sl, torch, prob, tier, init, steps, warmup, tune_cache=None, single_reps=20, settle=10):
     """Time `steps` split steps (after `warmup`) of `prob` in `tier`: the
-    split step as the library runs it (the (x1, x2) sweep pairs fused into one
-    pass each), then the same steps with every sweep its own pass (the
+    split step as the library runs it (the (x1, x2) and (v1, v2) sweep pairs fused
+    into one pass each), then the same steps with every sweep its own pass (the
     per-sweep figures)."""
     p = sl.Plan(prob.ns, prob.k, tier)
     mass0, hi0 = init
@@ -201,6 +202,10 @@ def run_tier(sl, torch, prob, tier, init, steps, warmup, tune_cache=None, single
         ms = ev0.elapsed_time(ev1) / steps
         per_dim = {d: p.timing_read(d) for d in range(prob.ndim)}
         fused = p.timing_read(-3)
+        # fused (v1, v2) pairs count among the sweeps along dimensions > 0 but
+        # under no single one
+        pair = tuple(a - sum(per_dim[d][i] for d in per_dim if d > 0)
+                     for i, a in enumerate(p.timing_read(-2)))
         p.timing_enable(False)
         kern = {}                   # kernel (template instance) -> (launches, total ms)
         for d, (n, tot) in per_dim.items():
@@ -210,8 +215,11 @@ def run_tier(sl, torch, prob, tier, init, steps, warmup, tune_cache=None, single
                 kern[name] = (n0 + n, t0 + tot)
         if fused[0]:
             kern[f"sldg::sweep_xy_kernel<{prob.k}, {tid}>"] = fused
+        if pair[0]:
+            kern[f"sldg::sweep_colpair_kernel<{prob.k}, {tid}>"] = pair
         key = "fused" if fuse else "unfused"
-        out[key] = {"ms_per_step": ms, "kernels": kern, "per_dim": per_dim, "fused": fused}
+        out[key] = {"ms_per_step": ms, "kernels": kern, "per_dim": per_dim, "fused": fused,
+                    "pair": pair}
     p.set_fusion(True)
     out["steps_run"] = 2 * (settle + warmup + steps)
     m_end = p.mass(bufs[cur][0])
@@ -658,7 +666,7 @@ def main():
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic, "kernel": kname, "launches": nl,
-                "sweeps_per_launch": 2 if "sweep_xy_kernel" in kname else 1,
+                "sweeps_per_launch": 2 if "_xy_" in kname or "_colpair_" in kname else 1,
                 "avg_launch_ms": round(avg_ms, 4), "algorithmic_bytes_per_launch": launch_bytes,
                 "copy_GBps": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4),
                 "plane_copy_GBps": plane_gbs}
@@ -677,10 +685,13 @@ def main():
                                                    launch_shape=main_r["shapes"][d],
                                                    form=main_r["forms"][d],
                                                    single_call=main_r["single"].get(d))
-    per_pass = {}                      # the step as timed: (x1, x2) pairs fused
+    per_pass = {}                      # the step as timed: pairs fused
     nf, tf = main_r["fused"]["fused"]
     if nf:
         per_pass["X1X2 fused"] = dict(rate(tf, nf), sweeps=2)
+    np_, tp = main_r["fused"]["pair"]
+    if np_:
+        per_pass["V1V2 fused"] = dict(rate(tp, np_), sweeps=2)
     for d, (n, tot_d) in main_r["fused"]["per_dim"].items():
         if n:
             per_pass[names.get(d, str(d))] = dict(rate(tot_d, n), sweeps=1)
@@ -731,7 +742,7 @@ def main():
         "config": {"workload": f"vlasov-4d split step, {args.n}^4 cells, k=2, 81 coeffs/cell, "
                                f"6 sweeps + mass per step",
                    "storage": f"mass f64 + modes {args.tier}", "parallelism": "single GPU",
-                   "step": "X1 X2 V1 V2 X1 X2, each (X1, X2) pair as one fused pass"},
+                   "step": "X1 X2 V1 V2 X1 X2, each (X1, X2) pair and (V1, V2) as one fused pass"},
         "roofline": roofline,
         "per_pass": per_pass,
         "per_sweep": per_sweep,
