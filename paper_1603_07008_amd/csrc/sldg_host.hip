@@ -933,19 +933,26 @@ sldg_status sldg_plan_ex(sldg_plan_t* out, int ndim, const int64_t* ncells, int 
   int64_t max_n = 0;
   for (int e = 0; e < ndim; ++e) max_n = std::max<int64_t>(max_n, ncells[e]);
   p->table_cap = std::max<int64_t>(cells / min_n, (int64_t)(k + 1) * max_n);
-  // default launch shape (measured on MI355X for the 4D k = 2 workload; the
-  // tuner picks per dimension), overridable from the environment
+  // Default launch shape (the tuner picks per dimension), overridable from the
+  // environment.  From 3/4 million cells of four dimensions on, 8 rows a thread
+  // and 2 column waves, staged for the 16-bit tiers: fewer halo rows and waves,
+  // where there are waves enough (48^4, k = 2: scaled FP16 432-567 us a strided
+  // sweep against 646-671, BF16 356-431 against 413-477, FP32 equal; 36 x 32 x 30
+  // x 27 5-10% less).  Smaller grids and fewer dimensions have too few waves
+  // (64^3, k = 2: 18-24 us against 13-16).
   int rows = 4, tuples = 9, colwaves = 1;
+  if (ndim >= 4 && cells >= 3 << 18) {
+    rows = 8;
+    colwaves = 2 | (elem_size(tier) == 2 ? SLDG_SHAPE_STAGED : 0);
+  }
   p->xcd_contig = 8;           // run lengths measured best on MI355X (4D k = 2)
   p->xcd_strided = 16;
   p->fuse = 1;
   p->xy_rows = 0;
   p->xcd_xy = 0;               // the fused pass: dispatch order measured best
-  p->xcd_strang = 16;          // 2048^2 k = 3 FP32-mode: 0.173 ms a pass against 0.199 in dispatch order
+  p->xcd_strang = 8;          // 2048^2 k = 3 FP32-mode: 0.173 ms a pass against 0.199 in dispatch order
   if (const char* env = getenv("SLDG_XY_ROWS")) p->xy_rows = std::max(0, atoi(env));
   if (const char* env = getenv("SLDG_XCD_XY")) p->xcd_xy = std::max(0, atoi(env));
-  p->xcd_strang = 8;
-
   if (const char* env = getenv("SLDG_COLWAVES")) {
     const int c = atoi(env);
     if (colwaves_valid(c)) colwaves = c;
