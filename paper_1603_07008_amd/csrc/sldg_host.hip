@@ -950,7 +950,7 @@ sldg_status sldg_plan_ex(sldg_plan_t* out, int ndim, const int64_t* ncells, int 
   p->fuse = 1;
   p->xy_rows = 0;
   p->xcd_xy = 0;               // the fused pass: dispatch order measured best
-  p->xcd_strang = 8;          // 2048^2 k = 3 FP32-mode: 0.173 ms a pass against 0.199 in dispatch order
+  p->xcd_strang = 16;          // 2048^2 k = 3 FP32-mode: 0.172 ms a pass, 0.174 at 8, 0.199 in dispatch order
   if (const char* env = getenv("SLDG_XY_ROWS")) p->xy_rows = std::max(0, atoi(env));
   if (const char* env = getenv("SLDG_XCD_XY")) p->xcd_xy = std::max(0, atoi(env));
   if (const char* env = getenv("SLDG_COLWAVES")) {
