@@ -23,8 +23,8 @@
 // column (128 x 100^2, shifts to +-10) that costs more than the two sweeps do
 // (k = 2 FP32 311 us against 170); to +-3, k = 2, it still costs less.
 //
-// Bound by memory: 48^4, k = 2 moves 3.4 GB in 732 us (4.7 TB/s; it reads 1.5 x
-// the state, L + 2 rows per L being shared through the caches) where the two
+// Bound by memory: 48^4, k = 2 moves 3.4 GB in 732 us (4.8 TB/s; it reads 1.4 x
+// the state: 10 rows of d per workgroup of 8, R + 3 of d + 1) where the two
 // sweeps take 668 + 693; bf16 436 (416 + 415), FP16 461 (443 + 448), FP64 at 40^4
 // 694 (643 + 691); k = 1 FP32 155 (140 + 150); 24^4, k = 3 FP32 203 (158 + 157).
 // The registers set L: more rows or waves spill (k = 2 FP64 at two waves a SIMD:
