@@ -219,8 +219,11 @@ sldg_status sldg_split_steps_adjoint(sldg_plan_t plan, const sldg_sweep_desc* se
                                      void* hi1, int* result_buffer);
 
 /* Fusion of sweeps inside sldg_split_steps and sldg_split_steps_adjoint:
- * enable != 0 on (the default), 0 off (every sweep its own pass).  Errors:
- * SLDG_ERR_ARG. */
+ * enable != 0 on (the default), 0 off (every sweep its own pass).  Off is the
+ * faster choice where the displacements along the later dimension change by
+ * more than about two cells over 64 neighbouring columns (fields far above one
+ * cell a step, on coarse grids): X V X and pair passes then do the work of each
+ * distinct shift, or read scattered rows.  Errors: SLDG_ERR_ARG. */
 sldg_status sldg_plan_set_fusion(sldg_plan_t plan, int enable);
 
 /*

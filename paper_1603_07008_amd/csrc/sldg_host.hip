@@ -667,6 +667,12 @@ constexpr int32_t kStrangRows = 8;
 // (sldg_strang.h): at most the cell mean FP64, a spectator group's planes
 // below 2^31 bytes and a launchable grid.  Kernel timing measures the sweeps
 // one by one, so it keeps them apart.
+// The displacements are on the device, so the rule cannot see them: it takes the
+// fields of ordinary steps (up to some cells, a few values over 64 columns;
+// 512^2, k = 2, FP32, shifts to 1.5 cells 15 us a step against 25 for three
+// sweeps, to 3 cells 21).  Wider spreads cost a pass per distinct shift of a
+// wave: to 10 cells over 512 columns 40 us against 26, over 2048 columns 76
+// against 115; sldg_plan_set_fusion turns the pass off.
 bool strang_eligible(const sldg_plan_s* p, StrangArgs& x, int64_t& nblocks) {
   if (!p->fuse || p->timing || p->ndim < 2 || p->n_lo > 1) return false;
   const int64_t N0 = p->n[0], N1 = p->n[1];
