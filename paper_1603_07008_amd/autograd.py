@@ -28,6 +28,16 @@ import torch
 from . import Plan, hi_dtype
 
 
+def _runs(nsteps, checkpoint_every, single):
+    """(first step, steps) of the forward pass's calls: a new one at every step
+    n with n % checkpoint_every == 0 (whatever the sign or number type of the
+    interval), or at every step if `single` (the fields of each step are its
+    own).  With fixed fields the steps between two checkpoints are one call."""
+    starts = [n for n in range(nsteps)
+              if n == 0 or single or (checkpoint_every and n % checkpoint_every == 0)]
+    return [(n, end - n) for n, end in zip(starts, starts[1:] + [nsteps])]
+
+
 class _SplitSteps(torch.autograd.Function):
     @staticmethod
     def forward(ctx, mass, hi, plan, seq, nsteps, checkpoint_every, frozen_shifts_fn):
@@ -35,15 +45,13 @@ class _SplitSteps(torch.autograd.Function):
         idx = 0
         ckpts = []
         seqs = []
-        # with fixed fields the steps between two checkpoints are one call
-        run = 1 if frozen_shifts_fn is not None else checkpoint_every or max(nsteps, 1)
-        for n in range(0, nsteps, run):
+        for n, run in _runs(nsteps, checkpoint_every, frozen_shifts_fn is not None):
             if checkpoint_every and n % checkpoint_every == 0:
                 ckpts.append((n, cur[idx][0].clone(), cur[idx][1].clone()))
             step_seq = seq if frozen_shifts_fn is None else frozen_shifts_fn(cur[idx])
             if frozen_shifts_fn is not None and not checkpoint_every:
                 seqs.append(step_seq)
-            res = plan.split_steps(step_seq, min(run, nsteps - n), cur[idx], cur[1 - idx])
+            res = plan.split_steps(step_seq, run, cur[idx], cur[1 - idx])
             idx = idx if res == 0 else 1 - idx
         ctx.plan = plan
         ctx.seq = seq
@@ -67,7 +75,8 @@ class _SplitSteps(torch.autograd.Function):
                 g, tmp = tmp, g
 
         if ctx.shifts_fn is None:
-            adjoint_steps(ctx.seq, ctx.nsteps)
+            if ctx.nsteps > 0:
+                adjoint_steps(ctx.seq, ctx.nsteps)
         elif not ctx.checkpoint_every:
             for step_seq in reversed(ctx.seqs):
                 adjoint_steps(step_seq, 1)
