@@ -19,8 +19,10 @@
 //               Where the wave's shifts take at most two neighbouring values
 //               smin, smin + 1 (modulo N1), as a smooth field gives, row r
 //               reads the X-swept rows r - smin, r - smin - 1, r - smin - 2:
-//               each row is loaded (one row ahead) and X-swept once.  Other
-//               waves evaluate the two rows of every distinct shift, per row.
+//               each row is loaded (one row ahead) and X-swept once.  In
+//               other waves each lane walks the rows of its own shift: it
+//               X-sweeps its own cell of row r - s, loading that cell, its
+//               lower neighbour's and the row's matrices itself.
 //   X after V   again takes the second source from the lane below.
 // The output cells of a row are the wave's columns moved by the row's X shifts:
 // the columns, and the V matrices held for them, stay fixed while the outputs
@@ -34,6 +36,14 @@
 // the batched Landau workload's step took 2.33 ms sweep by sweep, 1.10 ms with
 // the X-swept rows and the V-swept row in LDS (256 lanes, one barrier a row),
 // 0.95 ms in this form.
+// Waves of spread shifts load each X-swept cell's two sources (2 o^2 values) and
+// the row's matrices per lane, whatever the number of shifts: a step of 512^2,
+// k = 2, FP32, displacements to 3, 10 and 30 cells 15, 18 and 25 us (13 us to
+// 1.5 cells; three sweeps 24), 256^2, k = 3, BF16 12, 14 and 20 (25-31); 2048^2,
+// k = 2, FP32 106, 132 and 178 (222).  Evaluating both rows of every distinct
+// shift of the wave took 19, 37 and 101 us on the first of these.  Slower than the
+// sweeps: k = 3 at 512^2 and 30 cells, where a wave's lanes lie on some 24 rows
+// (42 us against 35).
 #pragma once
 
 #include "sldg_fused.h"
@@ -91,10 +101,11 @@ inline void strang_tiles(StrangArgs& a, int32_t rows) {
   a.nstrip = (a.N1 + a.R - 1) / a.R;
 }
 
-// Waves per SIMD the kernels are compiled for (their registers: 227 for FP32
-// at k = 3, 128 at k = 2, 63 at k = 1).
+// Waves per SIMD the kernels are compiled for (their registers: 256 for FP32
+// at k = 3, 128 at k = 2, 80 at k = 1; 16-bit k = 3 takes 217, and at three
+// waves it spills, 2048^2 190 us a step against 138).
 constexpr int strang_waves_per_simd(int k, int tier) {
-  return k == 3 ? (tier == 0 ? 1 : tier == 1 ? 2 : 3) : k == 2 ? (tier == 0 ? 3 : 4) : 6;
+  return k == 3 ? (tier == 0 ? 1 : 2) : k == 2 ? (tier == 0 ? 3 : 4) : 6;
 }
 
 // Tables at wave-uniform entries, read through the constant address space:
@@ -261,11 +272,12 @@ struct StrangCell {
   }
 };
 
-// The X sweep of a row in place: the lane's own source is its cell, the other
-// one the lane below's.
+// The X sweep of a row in place: the lane's own source is its cell q, the other
+// one y, or the lane below's where y is q itself.
 template <int K, int TIER, int H64>
 __device__ __forceinline__ void strang_x(float one, const Mat<K, TIER>& M,
-                                         const Rows64<K, 1>& R64, StrangCell<K, TIER, H64>& q) {
+                                         const Rows64<K, 1>& R64, StrangCell<K, TIER, H64>& q,
+                                         const StrangCell<K, TIER, H64>* yc = nullptr) {
   constexpr int O = K + 1;
   using T = typename Tier<TIER>::T;
 #pragma unroll
@@ -276,8 +288,8 @@ __device__ __forceinline__ void strang_x(float one, const Mat<K, TIER>& M,
 #pragma unroll
       for (int l0 = 0; l0 < O; ++l0) {
         raw_set<K, TIER, ND>(x, l0, l0 < ND ? T(0) : q.u[l1][l0], l0 < ND ? q.d : 0.0, one);
-        raw_set<K, TIER, ND>(y, l0, l0 < ND ? T(0) : lane_below(q.u[l1][l0]),
-                             l0 < ND ? lane_below(q.d) : 0.0, one);
+        raw_set<K, TIER, ND>(y, l0, l0 < ND ? T(0) : yc ? yc->u[l1][l0] : lane_below(q.u[l1][l0]),
+                             l0 < ND ? (yc ? yc->d : lane_below(q.d)) : 0.0, one);
       }
       strang_tuple<K, TIER, ND>(M, R64, x, y, q.u[l1], q.d, one);
     };
@@ -405,42 +417,72 @@ __device__ __forceinline__ void strang_body(const StrangArgs& a, int32_t tile, i
   // lane i: the shift of the X sweep after V for row r0 + i
   const int32_t sp = as_global(a.x1.s)[tb1 + step1 * min(r0 + c, N1 - 1)];
 
+  auto next_row = [&](int32_t q) { return q + 1 == n1 ? 0 : q + 1; };
   const int32_t s0 = __builtin_amdgcn_readfirstlane(sv);
   const int32_t up = s0 + 1 == n1 ? 0 : s0 + 1, dn = s0 == 0 ? n1 - 1 : s0 - 1;
   const bool two_up = __all(sv == s0 || sv == up);
   if (!two_up && !__all(sv == s0 || sv == dn)) {
-    // shifts all over: the two source rows of every distinct one, per row
-    for (int32_t r = r0; r < r1; ++r) {
-      Cell w{};
-      uint64_t todo = ~0ull;
-      while (todo) {
-        const int32_t s = __builtin_amdgcn_readlane(sv, __ffsll((unsigned long long)todo) - 1);
-        todo &= ~__ballot(sv == s);
-        int32_t row = r - s;
-        if (row < 0) row += n1;
-        Cell q[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          Mat<K, TIER> M;
-          Rows64<K, 1> R64;
-          mats0(row, M, R64);
-          fetch(q[i], row, PRE ? as_ctab(a.x0.s)[tb0 + step0 * row] : 0);
-          if constexpr (PRE) strang_x<K, TIER, H64>(one, M, R64, q[i]);
-          row = row == 0 ? n1 - 1 : row - 1;
-        }
-        Cell v;
-        strang_v<K, TIER, H64>(one, MV, RV, false, q[0], q[1], q[0], q[1], v);
-        const bool mine = sv == s;
-        w.d = mine ? v.d : w.d;
-#pragma unroll
-        for (int l1 = 0; l1 < O; ++l1)
-#pragma unroll
-          for (int l0 = 0; l0 < O; ++l0) w.u[l1][l0] = mine ? v.u[l1][l0] : w.u[l1][l0];
+    // shifts all over: every lane walks the source rows of its own shift, and
+    // X-sweeps its own cell of them, from that cell and its lower neighbour's
+    int32_t row = r0 - sv - 1;
+    if (row < 0) row += n1;
+    int32_t sn = PRE ? as_global(a.x0.s)[tb0 + step0 * row] : 0;
+    Cell S, Y;                                      // the cells of row `row`
+    int32_t at = 0;                                 // ... and its table entry
+    auto gather = [&] {
+      const uint32_t line = (uint32_t)row * (uint32_t)n0;
+      int32_t ix = col;
+      if constexpr (PRE) {
+        ix -= sn;
+        if (ix < 0) ix += n0;
+        Y.load(in, line + (uint32_t)(ix == 0 ? n0 - 1 : ix - 1));
+        at = tb0 + step0 * row;
       }
+      S.load(in, line + (uint32_t)ix);
+      row = next_row(row);
+      if constexpr (PRE) sn = as_global(a.x0.s)[tb0 + step0 * row];
+    };
+    auto swept = [&](Cell& q) {
+      if constexpr (PRE) {
+        Mat<K, TIER> M;
+        Rows64<K, 1> R64;
+        const auto* ab = as_global(a.x0.ab) + (int64_t)at * (2 * O2);
+#pragma unroll
+        for (int j = 0; j < O; ++j)
+#pragma unroll
+          for (int l = 0; l < O; ++l) {
+            const double A = ab[j * O + l], B = ab[O2 + j * O + l];
+            M.Aa[j][l] = (typename Tier<TIER>::Acc)A;
+            M.Ba[j][l] = (typename Tier<TIER>::Acc)B;
+            if (H64 && j == 0) {
+              R64.A[0][l] = A;
+              R64.B[0][l] = B;
+            }
+          }
+        strang_x<K, TIER, H64>(one, M, R64, S, &Y);
+      }
+      q = S;
+    };
+    Cell old, cur;
+    gather();
+    swept(old);
+    gather();
+    swept(cur);
+    gather();
+    auto step = [&](int32_t r, Cell& o, const Cell& c) {
       Mat<K, TIER> M1;
       Rows64<K, 1> R1;
       load_uniform<K, TIER, H64>(ab1, step1 * r, M1, R1);
+      Cell w;
+      strang_v<K, TIER, H64>(one, MV, RV, false, c, o, c, o, w);
       finish(r, __builtin_amdgcn_readlane(sp, r - r0), M1, R1, w);
+      swept(o);
+      gather();
+    };
+    for (int32_t r = r0; r < r1; r += 2) {
+      step(r, old, cur);
+      if (r + 1 >= r1) break;
+      step(r + 1, cur, old);
     }
     return;
   }
@@ -452,7 +494,6 @@ __device__ __forceinline__ void strang_body(const StrangArgs& a, int32_t tile, i
   int32_t row = r0 - smin - 2;
   while (row < 0) row += n1;
   const int32_t sx = PRE ? as_global(a.x0.s)[tb0 + step0 * ((row + c) % N1)] : 0;
-  auto next_row = [&](int32_t q) { return q + 1 == n1 ? 0 : q + 1; };
   const int32_t row1 = next_row(row), row2 = next_row(row1);
   Cell q0, q1, q2, S;
   fetch(q0, row, __builtin_amdgcn_readlane(sx, 0));

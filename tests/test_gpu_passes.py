@@ -1,0 +1,154 @@
+"""Fused passes of split steps beyond what the forward comparisons show: that
+the fused path is the one that runs (kernels of a captured call), transposed
+steps bitwise the transposed sweeps in two and more dimensions, and the time of
+a pass at displacements of many cells against the sweeps it replaces."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from gpu_helpers import have_gpu
+from test_gpu_strang import _bits, _seq, _state
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sl():
+    if not have_gpu():
+        pytest.skip("no HIP device")
+    import paper_1603_07008_amd as sl
+    sl.lib()
+    return sl
+
+
+def _kernels(stream, fn):
+    """Nodes of the graph that fn's launches on `stream` capture to."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t()
+    st = ctypes.c_void_p(stream.cuda_stream)
+    assert hip.hipStreamBeginCapture(st, 1) == 0           # thread-local
+    try:
+        fn()
+    finally:
+        assert hip.hipStreamEndCapture(st, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("ns,steps,fused,single", [((75, 41), 5, 1, 3), ((64,), 7, None, 1)])
+@pytest.mark.parametrize("adjoint", [False, True])
+def test_fused_launches(sl, ns, steps, fused, single, adjoint):
+    """X V X: one launch a step instead of three; a 1D plan's steps: one launch
+    in all (after the tables' one)."""
+    import torch
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        plan = sl.Plan(ns, 2, "fp32", stream=stream.cuda_stream)
+        a, b = plan.empty_state(), plan.empty_state()
+        seq = _seq(ns, 2, 1, 3.0, 0.4, 1) if len(ns) > 1 else \
+            [(0, 0, torch.full((1,), 0.3, dtype=torch.float64, device="cuda"))]
+        run = plan.split_steps_adjoint if adjoint else plan.split_steps
+        stream.synchronize()
+        for fuse, want in ((True, 1 if fused is None else steps * fused), (False, steps * single)):
+            plan.set_fusion(fuse)
+            assert _kernels(stream, lambda: run(seq, steps, a, b)) == want + 1
+        stream.synchronize()
+        plan.close()
+
+
+def _adjoint_both(sl, ns, k, tier, seq, nsteps, ndouble=1):
+    import torch
+    plan = sl.Plan(ns, k, tier, ndouble=ndouble)
+    st = _state(plan, 11)
+    a = tuple(t.clone() for t in st)
+    b = tuple(torch.full_like(t, float("nan")) for t in st)
+    got = (a, b)[plan.split_steps_adjoint(seq, nsteps, a, b)]
+    buf, cur = [tuple(t.clone() for t in st), plan.empty_state()], 0
+    for _ in range(nsteps):
+        for dim, mask, shift in reversed(seq):
+            plan.advect_dim_adjoint(dim, shift, mask, *buf[cur], *buf[1 - cur])
+            cur = 1 - cur
+    torch.cuda.synchronize()
+    for x, y in zip(got, buf[cur]):
+        assert torch.equal(_bits(x), _bits(y)), (ns, k, tier)
+    plan.close()
+
+
+@pytest.mark.parametrize("tier", ["fp64", "fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("k", [1, 2, 3])
+@pytest.mark.parametrize("amp", [0.4, 25.0])
+def test_transposed_x_v_x(sl, tier, k, amp):
+    """One and two V shifts to a wave, and a shift of its own per column."""
+    ns = (75, 41)
+    _adjoint_both(sl, ns, k, tier, _seq(ns, 2, 1, 9.0, amp, k), 3, ndouble=k % 2)
+
+
+@pytest.mark.parametrize("ns,mask_x,mask_v", [((1, 9), 2, 1), ((130, 1), 2, 1), ((66, 9), 0, 0),
+                                              ((21, 6, 5), 0b110, 0b101),
+                                              ((10, 6, 4, 3), 0b1010, 0b0101)])
+def test_transposed_masks_and_higher_dimensions(sl, ns, mask_x, mask_v):
+    for tier, k in (("fp32", 1), ("fp64", 2)):
+        _adjoint_both(sl, ns, k, tier, _seq(ns, mask_x, mask_v, 3.0, 40.0, 5), 2)
+
+
+@pytest.mark.parametrize("n0", [1, 2, 63, 64, 65, 200])
+@pytest.mark.parametrize("tier,k", [("fp32", 3), ("fp16", 2), ("bf16", 3)])
+def test_spread_shifts(sl, n0, tier, k):
+    """Smooth fields of many cells, whose waves hold runs of equal shifts, over
+    lines of less than one tile to several; odd and even numbers of rows."""
+    import torch
+    for n1 in (1, 5, 50):
+        ns = (n0, n1)
+        seq = _seq(ns, 2, 1, 1.5 * n0, 0.0, n0)
+        u = torch.arange(n0, dtype=torch.float64, device="cuda") / n0
+        seq[1] = (1, 1, 11.3 * torch.sin(2 * np.pi * u + 0.3))
+        plan = sl.Plan(ns, k, tier)
+        st = _state(plan, 5)
+        out = []
+        for fuse in (False, True):
+            plan.set_fusion(fuse)
+            a = tuple(t.clone() for t in st)
+            b = tuple(torch.full_like(t, float("nan")) for t in st)
+            out.append((a, b)[plan.split_steps(seq, 2, a, b)])
+        torch.cuda.synchronize()
+        for x, y in zip(*out):
+            assert torch.equal(_bits(x), _bits(y)), ns
+        plan.close()
+
+
+def _time(plan, seq, nsteps, a, b):
+    import torch
+    plan.split_steps(seq, nsteps, a, b)
+    best = float("inf")
+    for _ in range(5):
+        e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
+        e0.record()
+        plan.split_steps(seq, nsteps, a, b)
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1))
+    return best
+
+
+@pytest.mark.parametrize("k,tier", [(2, "fp32"), (3, "bf16"), (3, "fp64")])
+@pytest.mark.parametrize("amp", [3.0, 10.0, 30.0])
+def test_x_v_x_of_many_cells_costs_no_more_than_the_sweeps(sl, k, tier, amp):
+    """Measured ratios 0.5 to 1.2 (1.2: k = 3 at 30 cells); evaluating each
+    distinct shift of a wave by itself took 1.5 to 9 times the sweeps."""
+    import torch
+    ns = (512, 512)
+    plan = sl.Plan(ns, k, tier)
+    a, b = plan.empty_state(), plan.empty_state()
+    for t in (*a, *b):
+        t.zero_()
+    u = torch.arange(512, dtype=torch.float64, device="cuda") / 512
+    sx = 4.0 * (2.0 * u - 1.0)
+    seq = [(0, 2, sx), (1, 1, amp * torch.sin(2 * np.pi * u)), (0, 2, sx)]
+    t = []
+    for fuse in (False, True):
+        plan.set_fusion(fuse)
+        t.append(_time(plan, seq, 10, a, b))
+    assert t[1] <= 1.4 * t[0], t
+    plan.close()
