@@ -568,11 +568,16 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
   // X V X passes, and the entry-major matrices of their X sweeps
   b->triple.assign((size_t)nseq, 0);
   b->pass.assign((size_t)nseq * b->nprob, PassInfo{});
-  int64_t tot_em = 0;
+  int64_t tot_em = 0, lines = 0;
+  for (int p = 0; p < b->nprob; ++p)
+    lines += (ext(b, p)[0] + 61) / 62 * (b->cells[p] / ext(b, p)[0]) * b->modes[p] /
+             ((b->k[p] + 1) * (b->k[p] + 1));
   for (int q = 0; q + 2 < nseq; ++q) {
     if (dims[q] != 0 || dims[q + 1] != 1 || dims[q + 2] != 0) continue;
     for (int p = 0; p < b->nprob; ++p) {
-      if (!strang_fits(b->cells[p], b->k[p] + 1, elem_size(b->tier))) continue;
+      if (!strang_fits(b->cells[p], b->k[p] + 1, elem_size(b->tier)) ||
+          !strang_pays(b->k[p], elem_size(b->tier), ext(b, p)[0], lines))
+        continue;
       PassInfo& pi = b->pass[(size_t)q * b->nprob + p];
       pi.on = true;
       b->triple[(size_t)q] = 1;

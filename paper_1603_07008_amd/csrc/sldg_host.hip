@@ -682,6 +682,7 @@ bool strang_eligible(const sldg_plan_s* p, StrangArgs& x, int64_t& nblocks) {
   x.Q = (int32_t)(p->cells / (N0 * N1));
   const int64_t groups = p->modes / (p->o * p->o);
   const int64_t lines = (N0 + 61) / 62 * x.Q * groups * N1;    // wave rows
+  if (!strang_pays(p->k, elem_size(p->tier), N0, lines)) return false;
   int32_t rows = kStrangRows;
   while (rows > 1 && lines / rows < kStrangWaves) rows >>= 1;
   strang_tiles(x, rows);

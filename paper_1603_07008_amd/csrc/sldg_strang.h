@@ -89,6 +89,20 @@ inline bool strang_fits(int64_t cells, int64_t o, int64_t size) {
   return o * o * cells * size <= (int64_t)INT32_MAX && cells * 8 <= (int64_t)INT32_MAX;
 }
 
+// Whether a pass over grids of `lines` wave rows in all pays for lines of N0
+// cells: its tiles take 64 lanes whatever their cells, so short lines leave lanes
+// idle, which costs where the chip is full.  Measured (smooth displacements, a
+// step as a pass and as three sweeps): 4 x 1024 x 64, k = 2, FP32 118 and 47 us, 8
+// cells 64 and 44, 16 cells 38 and 43; k = 3, BF16 16 cells 97 and 61, 20 cells 84
+// and 65, 24 cells 85 and 89; k = 1, BF16 8 cells 22 and 20; FP64 at k = 3 8 cells
+// 263 and 156, 16 cells 142 and 169.  Small grids wait for launches instead (4 x
+// 4096, k = 3, FP32: 14 us and 27).
+constexpr int64_t kStrangFull = 16384;
+inline bool strang_pays(int k, int64_t size, int64_t N0, int64_t lines) {
+  const int64_t nt = (N0 + 61) / 62, C = (N0 + nt - 1) / nt;
+  return lines < kStrangFull || C >= (size == 8 ? 4 * k + 4 : k == 1 ? 12 : k == 2 ? 20 : 24);
+}
+
 constexpr int kStrangMaxRows = 60;        // a strip's shifts (R + 4 rows) in one wave's lanes
 
 // Tiles of dimension 0: the fewest of at most 62 cells; strips of `rows` rows.

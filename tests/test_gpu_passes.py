@@ -58,6 +58,26 @@ def test_fused_launches(sl, ns, steps, fused, single, adjoint):
         plan.close()
 
 
+@pytest.mark.parametrize("ns,k,tier,fused", [
+    ((4, 1024, 64), 2, "fp32", False), ((8, 512, 64), 3, "bf16", False),
+    ((16, 64, 256), 3, "fp32", False), ((30, 100, 64), 3, "bf16", True),
+    ((16, 64, 256), 2, "fp64", True), ((8, 500), 3, "bf16", True), ((4, 4096), 2, "fp32", True)])
+def test_x_v_x_of_short_lines(sl, ns, k, tier, fused):
+    """Full-chip grids of lines that fill few lanes run sweep by sweep (4 x 1024 x
+    64: a pass took 2.5 times the sweeps); the others in one pass."""
+    import torch
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        plan = sl.Plan(ns, k, tier, stream=stream.cuda_stream)
+        a, b = plan.empty_state(), plan.empty_state()
+        seq = _seq(ns, 2, 1, 3.0, 0.4, 1)
+        stream.synchronize()
+        n = _kernels(stream, lambda: plan.split_steps(seq, 2, a, b))
+        assert n == (3 if fused else 7)
+        stream.synchronize()
+        plan.close()
+
+
 def _adjoint_both(sl, ns, k, tier, seq, nsteps, ndouble=1):
     import torch
     plan = sl.Plan(ns, k, tier, ndouble=ndouble)
@@ -152,3 +172,33 @@ def test_x_v_x_of_many_cells_costs_no_more_than_the_sweeps(sl, k, tier, amp):
         t.append(_time(plan, seq, 10, a, b))
     assert t[1] <= 1.4 * t[0], t
     plan.close()
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_with_problems_outside_the_pass(sl, graph):
+    """A batch that fills the chip: its problems of short lines run sweep by sweep
+    beside the others' passes, bitwise each problem's sweeps."""
+    import torch
+    from paper_1603_07008_amd.batch import Batch
+    grids = [((8, 9000), 3), ((130, 3000), 2), ((6, 4000), 1), ((40, 50), 3), ((10, 37), 2)]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        seqs = [_seq(ns, 2, 1, 3.0, 2.5, i) for i, (ns, _) in enumerate(grids)]
+        plans = [sl.Plan(ns, k, "fp32", stream=stream.cuda_stream) for ns, k in grids]
+        states = [_state(p, i) for i, p in enumerate(plans)]
+        b = Batch([g[0] for g in grids], [g[1] for g in grids], "fp32", stream=stream.cuda_stream)
+        s0 = [tuple(t.clone() for t in st) for st in states]
+        s1 = [tuple(torch.full_like(t, float("nan")) for t in st) for st in states]
+        b.bind(s0, s1)
+        b.set_sequence([(seqs[0][q][0], [(s[q][1], s[q][2]) for s in seqs]) for q in range(3)])
+        res = b.run(3, use_graph=graph)
+        for i, plan in enumerate(plans):
+            plan.set_fusion(False)
+            x = tuple(t.clone() for t in states[i])
+            y = plan.empty_state()
+            want = (x, y)[plan.split_steps(seqs[i], 3, x, y)]
+            stream.synchronize()
+            for got, ref in zip((s0, s1)[res][i], want):
+                assert torch.equal(_bits(got), _bits(ref)), grids[i]
+            plan.close()
+        b.close()
