@@ -25,7 +25,7 @@ SOURCES = [os.path.join(CSRC, f) for f in PLAIN + INST]
 HEADERS = [os.path.join(CSRC, f) for f in ("sldg_internal.h", "sldg_sweep.h", "ab_poly.h",
                                           "sldg_ref.h", "sldg_field.h", "sldg_colloc.h",
                                           "sldg_fused.h", "sldg_staged.h", "sldg_strang.h",
-                                          "sldg_colpair.h", "sldg_line.h")] + \
+                                          "sldg_colpair.h", "sldg_colsweep.h", "sldg_line.h")] + \
     [os.path.join(ROOT, "include", "sldg.h")]
 ARCH = os.environ.get("SLDG_OFFLOAD_ARCH", "gfx950")
 

@@ -19,12 +19,11 @@
 // field), and each lane picks its window of the rows loaded for the wave: whole
 // rows instead of pieces of two (48^4, k = 2, FP32 840 us when every lane loads
 // its own L + 1 rows, 745 so; bf16 577 and 433).  Waves with other shifts load
-// each lane's own rows.  Where the shifts differ by half a cell from column to
-// column (128 x 100^2, shifts to +-10) that costs more than the two sweeps do
-// (k = 2 FP32 311 us against 170); to +-3, k = 2, it still costs less.
+// each lane's own rows, scattered over both dimensions; fields of more than a few
+// cells over a wave run the two sweeps by themselves instead (sldg_colsweep.h).
 //
 // Bound by memory: 48^4, k = 2 moves 3.4 GB in 732 us (4.8 TB/s; it reads 1.4 x
-// the state: 10 rows of d per workgroup of 8, R + 3 of d + 1) where the two
+// the state: 10 rows of d per workgroup of 8, R + 2 of d + 1) where the two
 // sweeps take 668 + 693; bf16 436 (416 + 415), FP16 461 (443 + 448), FP64 at 40^4
 // 694 (643 + 691); k = 1 FP32 155 (140 + 150); 24^4, k = 3 FP32 203 (158 + 157).
 // The registers set L: more rows or waves spill (k = 2 FP64 at two waves a SIMD:
@@ -47,7 +46,6 @@ struct ColPairArgs {
   int32_t R, nstrip;         // rows of d + 1 per wave, strips
   int32_t nblk;              // column blocks (64 columns) of a Q slab
   int32_t nchunk;            // workgroups along d: ceil(N1 / (4 L))
-  int32_t xcd;               // XCD-aware tile order: run length G (0 off)
   float one;                 // 1.0f: the FP16 tier's unit scale
   FastDiv fblk, fstrip, fchunk, fQ;
   const int32_t* s1;         // the two sweeps' line tables, component-major
@@ -58,6 +56,7 @@ struct ColPairArgs {
   const double* ab2;
   int64_t cs2;
   LineMap map2;
+  const int32_t* flag;       // the pass does nothing where *flag != 0 (may be null)
 };
 
 // Rows of dimension d per lane, and waves per SIMD (they bound the registers).
@@ -253,7 +252,7 @@ __device__ __forceinline__ void colpair_body(const ColPairArgs& a, int32_t blk, 
     mats.fill(1, a.ab2, a.cs2, t2, lane, wave);
   }
   __syncthreads();
-  if (b1 >= N1) return;
+  if (b1 >= N1 || (a.flag && *as_ctab(a.flag) != 0)) return;
   // a sweep's matrices, read again at each use
   auto get = [&](int i, Mat<K, TIER>& M, Rows64<K, 1>& R64) {
     asm volatile("" ::: "memory");
@@ -416,7 +415,7 @@ __global__ __launch_bounds__(256, colpair_waves_per_simd(K, TIER)) void sweep_co
     ColPairArgs a) {
   // tile order: the workgroups along d of a column block first (they share
   // rows), then the column blocks, strips, slabs and groups
-  const uint32_t w = xcd_tile(blockIdx.x, gridDim.x, a.xcd);
+  const uint32_t w = blockIdx.x;
   const uint32_t q1 = a.fchunk.div(w);
   const int32_t cg = (int32_t)(w - q1 * (uint32_t)a.nchunk);
   const uint32_t q2 = a.fblk.div(q1);

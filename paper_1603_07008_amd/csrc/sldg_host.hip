@@ -23,6 +23,7 @@
 #include "sldg_fused.h"
 #include "sldg_strang.h"
 #include "sldg_colpair.h"
+#include "sldg_colsweep.h"
 #include "sldg_line.h"
 
 using namespace sldg;
@@ -734,7 +735,7 @@ constexpr int64_t kPairBlocks = 512;
 // whether it pays.  That takes three quarters of the lanes (columns below d
 // over a whole number of waves: 48 of 64 columns x 160^2, k = 2, bf16: 65 us
 // against 74 for the two sweeps; 40 columns 62 against 57, 16 columns 61 against
-// 26), and four rows of d + 1 (a strip reads three more than it writes; 8192
+// 26), and four rows of d + 1 (a strip reads two more than it writes; 8192
 // columns x 64 x 4 rows 270 us against 316, x 2 rows 207 against 172).  For
 // k = 3 eight rows and seven eighths of the lanes: its waves hold one row of d
 // and read three (12^4 cells, 144 columns in 192 lanes, FP64: 50 us against 36;
@@ -770,14 +771,104 @@ bool colpair_eligible(const sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask
   x.R = (int32_t)((x.N2 + ns - 1) / ns);
   x.nstrip = (x.N2 + x.R - 1) / x.R;
   nblocks *= x.nstrip;
-  return nblocks <= INT32_MAX;
+  // lines of both dimensions that the sweeps one by one hold in LDS
+  ColSweepArgs line{};
+  int64_t lds = 0;
+  line.P = x.P;
+  line.N = std::max(x.N1, x.N2);
+  return nblocks <= INT32_MAX && p->cells / 8 * (p->modes / p->o) <= INT32_MAX &&
+         colsweep_tiles(line, (int)p->o, elem_size(p->tier), lds);
 }
 
-// The fused pair along d and d + 1; its tables are at entries pre1 and pre2 of
-// the plan's tables.
+// Spread flags of the pairs of a call: on the device, in the plan's scratch of
+// the mass reduction (both run on the plan's stream, and no pass comes between a
+// flag and its pair that reduces a mass).
+int64_t pair_flags(const sldg_plan_s* p) { return 4 * p->mass_nblocks; }
+int32_t* pair_flag(const sldg_plan_s* p, int i) {
+  return reinterpret_cast<int32_t*>(p->d_mass_part) + i;
+}
+
+// The mean span of the shifts of 64 columns (largest less smallest, + 1) from
+// which a pair's sweeps run one by one: the fused pass then reads scattered rows.
+// Pass and sweeps (the plan's own), us: 48^4, k = 2, FP32 at spans 2.4, 4.4, 7.5 and
+// 14 806, 1324, 2030, 4977 and 1346, 1402, 1513, 1771; BF16 546, 898, 1326, 2800 and
+// 732, 736, 744, 993; FP64 1519, 2088, 2848, 6070 and 2618, 2655, 2784, 3441; 24^4,
+// k = 3, FP32 at 2.4, 4.8 and 8.1 259, 449, 926 and 320, 383, 413; 128 x 100^2, k = 2,
+// FP32 at 5, 8 and 14 87, 122, 183 and 134, 141, 156.
+constexpr float pair_span(int k, sldg_tier tier) {
+  return tier == SLDG_TIER_FP64 ? 7.0f : k == 3 ? 4.0f : 4.5f;
+}
+
+// States up to which the fused pass runs at any displacements: they stay in the
+// caches, where scattered rows cost less than the launches of a choice (64^3, k =
+// 1, FP32, 10 MB: 15, 18 and 23 us at spans of 6, 10 and 18 against 21 for the
+// sweeps, 27 by line sweeps; 16^4, k = 1 10 us instead of 14; 64^3, k = 2, 30 MB 40
+// us at 6 and 49 at 10 against 37; 16^4, k = 2, BF16, 11 MB, 40 at 16 against 32).
+constexpr int64_t kPairSmall = 10 << 20;
+bool pair_decides(const sldg_plan_s* p) { return p->lo_bytes + p->hi_bytes > kPairSmall; }
+
+// Flag i: whether the pair along d and d + 1 with its tables at entries pre1 and
+// pre2 is too spread.
+sldg_status decide_colpair(sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask2, int64_t pre1,
+                           int64_t pre2, int i) {
+  if (!pair_decides(p)) return SLDG_OK;
+  PairSpread x{};
+  SweepArgs a1{}, a2{};
+  int64_t nt = 0;
+  describe(p, d, mask1, a1, nt);
+  describe(p, d + 1, mask2, a2, nt);
+  x.s1 = p->d_s + pre1;
+  x.s2 = p->d_s + pre2;
+  x.map1 = a1.map;
+  x.map2 = a2.map;
+  x.N1 = a1.N;
+  x.N2 = a2.N;
+  x.P = a1.P;
+  x.most = pair_span(p->k, p->tier);
+  const hipError_t e = launch_pair_spread(x, pair_flag(p, i), p->stream);
+  return e == hipSuccess ? SLDG_OK : device_error(e, "pair decision launch");
+}
+
+// One of the pair's sweeps by itself, where the flag is set (in place where the
+// buffers are the same).
+sldg_status run_colsweep(sldg_plan_s* p, int dim, uint32_t mask, int64_t pre, const int32_t* flag,
+                         const double* in_lo, const void* in_hi, double* out_lo, void* out_hi) {
+  SweepArgs a{};
+  ColSweepArgs x{};
+  describe(p, dim, mask, a, x.cs);
+  x.in_lo = in_lo;
+  x.in_hi = in_hi;
+  x.out_lo = out_lo;
+  x.out_hi = out_hi;
+  x.n_lo = (int32_t)p->n_lo;
+  x.cells = p->cells;
+  x.P = a.P;
+  x.N = a.N;
+  x.Q = a.Q;
+  x.ms = a.mstride;
+  int64_t lds = 0;
+  colsweep_tiles(x, (int)p->o, elem_size(p->tier), lds);
+  x.ntile = (a.P + (1 << x.logc) - 1) >> x.logc;
+  x.items = x.ntile * a.Q * a.nspec;
+  x.one = 1.0f;
+  x.ftile = FastDiv::make((uint32_t)x.ntile);
+  x.fQ = FastDiv::make((uint32_t)x.Q);
+  x.s = p->d_s + pre;
+  x.ab = p->d_ab + 2LL * p->o * p->o * pre;
+  x.map = a.map;
+  x.flag = flag;
+  const int32_t nblocks = (int32_t)std::min<int64_t>(x.items, 256 * std::min<int64_t>(8, kColSweepLdsMax / lds));
+  const hipError_t e = launch_colsweep(p->k, (int)p->tier, x, nblocks, (int32_t)lds, p->stream);
+  return e == hipSuccess ? SLDG_OK : device_error(e, "line sweep launch");
+}
+
+// The pair along d and d + 1, its tables at entries pre1 and pre2 of the plan's
+// tables: in one pass, or one sweep after the other through LDS lines where flag
+// i says that the shifts are too spread (large states).  The displacements are on the device, so
+// all three launches are issued and those not wanted leave at once.
 sldg_status run_colpair(sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask2, int64_t pre1,
-                        int64_t pre2, const double* in_lo, const void* in_hi, double* out_lo,
-                        void* out_hi) {
+                        int64_t pre2, int i, const double* in_lo, const void* in_hi,
+                        double* out_lo, void* out_hi) {
   ColPairArgs x{};
   int64_t nblocks = 0;
   if (!colpair_eligible(p, d, mask1, mask2, x, nblocks))
@@ -803,11 +894,16 @@ sldg_status run_colpair(sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask2, i
   x.fstrip = FastDiv::make((uint32_t)x.nstrip);
   x.fchunk = FastDiv::make((uint32_t)x.nchunk);
   x.fQ = FastDiv::make((uint32_t)x.Q);
+  x.flag = pair_decides(p) ? pair_flag(p, i) : nullptr;
   bool timed = false;
-  const sldg_status tst = timing_begin(p, timed);
-  if (tst != SLDG_OK) return tst;
+  sldg_status st = timing_begin(p, timed);
+  if (st != SLDG_OK) return st;
   const hipError_t e = launch_colpair(p->k, (int)p->tier, x, (int32_t)nblocks, p->stream);
   if (e != hipSuccess) return device_error(e, "fused sweep launch");
+  if (x.flag) st = run_colsweep(p, d, mask1, pre1, x.flag, in_lo, in_hi, out_lo, out_hi);
+  if (st == SLDG_OK && x.flag)
+    st = run_colsweep(p, d + 1, mask2, pre2, x.flag, out_lo, out_hi, out_lo, out_hi);
+  if (st != SLDG_OK) return st;
   return timing_end(p, timed, kPairTimingDim);
 }
 
@@ -1148,6 +1244,7 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
     int64_t nblocks = 0;
     ColPairArgs cp{};
     if (seq[q].dim > 0 && seq[q + 1].dim == seq[q].dim + 1 &&
+        pairs < pair_flags(p) &&
         colpair_eligible(p, seq[q].dim, seq[q].dep_mask, seq[q + 1].dep_mask, cp, nblocks)) {
       fused[(size_t)q] = 4;
       ++pairs;
@@ -1202,6 +1299,23 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
       for (int q = 0; q < nseq; ++q) pre[(size_t)q] = set.first[of[q]];
     }
   }
+  std::vector<int> flag((size_t)std::max(nseq, 1), 0);
+  for (int q = 0, i = 0; q + 1 < nseq; ++q) {
+    if (fused[(size_t)q] != 4 || pre[(size_t)q] < 0) continue;
+    // pairs with the same tables share a flag
+    int f = -1;
+    for (int e = 0; e < q && f < 0; ++e)
+      if (fused[(size_t)e] == 4 && pre[(size_t)e] == pre[(size_t)q] &&
+          pre[(size_t)e + 1] == pre[(size_t)q + 1])
+        f = flag[(size_t)e];
+    if (f < 0) {
+      f = i++;
+      const sldg_status st = decide_colpair(p, seq[q].dim, seq[q].dep_mask, seq[q + 1].dep_mask,
+                                            pre[(size_t)q], pre[(size_t)q + 1], f);
+      if (st != SLDG_OK) return st;
+    }
+    flag[(size_t)q] = f;
+  }
   int cur = 0;
   if (pre[0] >= 0 && (int64_t)nseq * nsteps > 1 && line_steps_eligible(p)) {
     const sldg_status st = run_line_steps(p, pre, nseq, (int64_t)nseq * nsteps, m, h, cur);
@@ -1228,7 +1342,7 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
         q += 2;
       } else if (fused[(size_t)q] == 4 && pre[(size_t)q] >= 0) {
         st = run_colpair(p, seq[q].dim, seq[q].dep_mask, seq[q + 1].dep_mask, pre[(size_t)q],
-                         pre[(size_t)q + 1], m[cur], h[cur], m[1 - cur], h[1 - cur]);
+                         pre[(size_t)q + 1], flag[(size_t)q], m[cur], h[cur], m[1 - cur], h[1 - cur]);
         ++q;
       } else {
         st = run_sweep(p, seq[q].dim, seq[q].shift, seq[q].dep_mask, m[cur], h[cur], m[1 - cur],
@@ -1980,8 +2094,10 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
   auto v_sweeps = [&](bool last) {
     sldg_status st;
     if (vpair && !(last && !result_buffer && nsteps % 2)) {
-      st = run_colpair(p, 2, dep[2], dep[3], pre[2], pre[3], m[cur], hh[cur], m[1 - cur],
-                       hh[1 - cur]);
+      st = decide_colpair(p, 2, dep[2], dep[3], pre[2], pre[3], 0);
+      if (st == SLDG_OK)
+        st = run_colpair(p, 2, dep[2], dep[3], pre[2], pre[3], 0, m[cur], hh[cur], m[1 - cur],
+                         hh[1 - cur]);
       if (st == SLDG_OK) cur = 1 - cur;
     } else {
       st = sweep(2);

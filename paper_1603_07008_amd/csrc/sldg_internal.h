@@ -191,6 +191,26 @@ struct ColPairArgs;
 hipError_t launch_colpair(int k, int tier, const ColPairArgs& a, int32_t nblocks, hipStream_t st);
 template <int K, int TIER>
 hipError_t launch_colpair_inst(const ColPairArgs& a, int32_t nblocks, hipStream_t st);
+// One of the pair's sweeps by itself, where its flag is set (sldg_colsweep.h):
+// nblocks persistent workgroups, lds bytes of LDS.
+struct ColSweepArgs;
+hipError_t launch_colsweep(int k, int tier, const ColSweepArgs& a, int32_t nblocks, int32_t lds,
+                           hipStream_t st);
+template <int K, int TIER>
+hipError_t launch_colsweep_inst(const ColSweepArgs& a, int32_t nblocks, int32_t lds,
+                                hipStream_t st);
+// *flag = whether the columns' shifts of a pair are spread: over the blocks of 64
+// of the P columns (at most kPairSample of them, evenly spaced), the mean of the
+// larger of the two sweeps' spans (largest less smallest shift, modulo the
+// extent, + 1) exceeds `most`.
+constexpr int32_t kPairSample = 512;
+struct PairSpread {
+  const int32_t *s1, *s2;
+  LineMap map1, map2;
+  int32_t N1, N2, P;
+  float most;
+};
+hipError_t launch_pair_spread(const PairSpread& a, int32_t* flag, hipStream_t st);
 // Sweeps of a 1D problem in one launch (sldg_line.h): one workgroup of `cells`
 // (1, 2, 4) cells a lane, lds bytes of LDS.
 struct LineStepsArgs;

@@ -426,6 +426,78 @@ hipError_t launch_colpair(int k, int tier, const ColPairArgs& a, int32_t nblocks
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_colsweep(int k, int tier, const ColSweepArgs& a, int32_t nblocks, int32_t lds,
+                           hipStream_t st) {
+#define SLDG_COLSWEEP_CALL(KK, TT) launch_colsweep_inst<KK, TT>(a, nblocks, lds, st)
+  switch (k) {
+    case 1:
+      switch (tier) {
+        case 0: return SLDG_COLSWEEP_CALL(1, 0);
+        case 1: return SLDG_COLSWEEP_CALL(1, 1);
+        case 2: return SLDG_COLSWEEP_CALL(1, 2);
+        case 3: return SLDG_COLSWEEP_CALL(1, 3);
+      }
+      break;
+    case 2:
+      switch (tier) {
+        case 0: return SLDG_COLSWEEP_CALL(2, 0);
+        case 1: return SLDG_COLSWEEP_CALL(2, 1);
+        case 2: return SLDG_COLSWEEP_CALL(2, 2);
+        case 3: return SLDG_COLSWEEP_CALL(2, 3);
+      }
+      break;
+    case 3:
+      switch (tier) {
+        case 0: return SLDG_COLSWEEP_CALL(3, 0);
+        case 1: return SLDG_COLSWEEP_CALL(3, 1);
+        case 2: return SLDG_COLSWEEP_CALL(3, 2);
+        case 3: return SLDG_COLSWEEP_CALL(3, 3);
+      }
+      break;
+  }
+#undef SLDG_COLSWEEP_CALL
+  return hipErrorInvalidValue;
+}
+
+// The span of a wave's shifts s (in [0, N)) modulo N: largest less smallest, + 1.
+__device__ __forceinline__ int32_t wave_span(int32_t s, int32_t N) {
+  int32_t d = s - __builtin_amdgcn_readfirstlane(s);
+  if (d > N / 2) d -= N;
+  if (d < -(N / 2)) d += N;
+  int32_t lo = d, hi = d;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = min(lo, __shfl_xor(lo, o));
+    hi = max(hi, __shfl_xor(hi, o));
+  }
+  return hi - lo + 1;
+}
+
+// One workgroup: a wave per column block in turn.
+__global__ __launch_bounds__(1024) void pair_spread_kernel(PairSpread a, int32_t* flag) {
+  __shared__ int64_t sh[16];
+  const int32_t lane = (int32_t)(threadIdx.x & 63), wave = (int32_t)(threadIdx.x >> 6);
+  const int32_t nblk = (a.P + 63) / 64, n = min(nblk, kPairSample);
+  int64_t sum = 0;
+  for (int32_t i = wave; i < n; i += 16) {
+    const int32_t b = (int32_t)((int64_t)i * nblk / n);
+    const int32_t col = min(b * 64 + lane, a.P - 1);
+    sum += max(wave_span(a.s1[table_index(a.map1, col, 0)], a.N1),
+               wave_span(a.s2[table_index(a.map2, col, 0)], a.N2));
+  }
+  if (lane == 0) sh[wave] = sum;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  sum = 0;
+  for (int w = 0; w < 16; ++w) sum += sh[w];
+  *flag = (double)sum > (double)a.most * n ? 1 : 0;
+}
+
+hipError_t launch_pair_spread(const PairSpread& a, int32_t* flag, hipStream_t st) {
+  pair_spread_kernel<<<1, 1024, 0, st>>>(a, flag);
+  return hipGetLastError();
+}
+
 hipError_t launch_line_steps(int k, int tier, const LineStepsArgs& a, int cells, int32_t lds,
                              hipStream_t st) {
 #define SLDG_LINE_CALL(KK, TT) launch_line_steps_inst<KK, TT>(a, cells, lds, st)
