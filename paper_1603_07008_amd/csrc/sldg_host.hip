@@ -955,6 +955,24 @@ sldg_status run_line_steps(sldg_plan_s* p, const std::vector<int64_t>& pre, int 
   return SLDG_OK;
 }
 
+// Default launch shape of a strided sweep (the tuner picks per dimension): 4 rows a
+// thread, or 8 with 2 column waves, which read fewer halo rows, on grids of 3/4
+// million cells of four dimensions on, along dimensions of 16 cells on whose last
+// chunk of 8 rows is not much emptier than of 4 (for k = 1, whose sweeps are
+// short, no emptier).  From 2^22 cells on staged for the 16-bit tiers.  Over 30
+// grids of 4 to 6 dimensions and every degree and tier 8 rows under this rule take
+// 0.87 (scaled FP16), 0.95 (BF16) and 0.96 (FP32, FP64) of the time of 4 rows, one
+// sweep in a hundred 3-11% more; without it the same shape costs 1024 x 8 x 10 x 10,
+// k = 3, BF16 350 us against 288 (10 rows in chunks of 8) and, staged, 64^3 x 3, k =
+// 2, BF16 59 us against 48.  48^4, k = 2: scaled FP16 432-567 us a strided sweep
+// against 646-671, BF16 356-431 against 413-477.  Smaller grids and fewer dimensions
+// have too few waves (64^3, k = 2: 18-24 us against 13-16).
+bool eight_rows(const sldg_plan_s* p, int d) {
+  if (p->ndim < 4 || p->cells < 3 << 18 || p->n[d] < 16) return false;
+  const int64_t pad4 = (p->n[d] + 3) / 4 * 4, pad8 = (p->n[d] + 7) / 8 * 8;
+  return p->k == 1 ? pad8 <= pad4 : 7 * pad8 <= 8 * pad4;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1036,18 +1054,8 @@ sldg_status sldg_plan_ex(sldg_plan_t* out, int ndim, const int64_t* ncells, int 
   int64_t max_n = 0;
   for (int e = 0; e < ndim; ++e) max_n = std::max<int64_t>(max_n, ncells[e]);
   p->table_cap = std::max<int64_t>(cells / min_n, (int64_t)(k + 1) * max_n);
-  // Default launch shape (the tuner picks per dimension), overridable from the
-  // environment.  From 3/4 million cells of four dimensions on, 8 rows a thread
-  // and 2 column waves, staged for the 16-bit tiers: fewer halo rows and waves,
-  // where there are waves enough (48^4, k = 2: scaled FP16 432-567 us a strided
-  // sweep against 646-671, BF16 356-431 against 413-477, FP32 equal; 36 x 32 x 30
-  // x 27 5-10% less).  Smaller grids and fewer dimensions have too few waves
-  // (64^3, k = 2: 18-24 us against 13-16).
-  int rows = 4, tuples = 9, colwaves = 1;
-  if (ndim >= 4 && cells >= 3 << 18) {
-    rows = 8;
-    colwaves = 2 | (elem_size(tier) == 2 ? SLDG_SHAPE_STAGED : 0);
-  }
+  // launch shape of every dimension from the environment, if set
+  int rows = 0, tuples = 9, colwaves = 0;
   p->xcd_contig = 8;           // run lengths measured best on MI355X (4D k = 2)
   p->xcd_strided = 16;
   p->fuse = 1;
@@ -1072,9 +1080,11 @@ sldg_status sldg_plan_ex(sldg_plan_t* out, int ndim, const int64_t* ncells, int 
     if (r == 1 || r == 2 || r == 4 || r == 8) rows = r;
   }
   for (int d = 0; d < kMaxDim; ++d) {
-    p->rows_d[d] = rows;
+    const bool eight = d < ndim && eight_rows(p, d);
+    const int stage = eight && elem_size(tier) == 2 && cells >= 1 << 22 ? SLDG_SHAPE_STAGED : 0;
+    p->rows_d[d] = rows > 0 ? rows : eight ? 8 : 4;
     p->tuples_d[d] = tuples;
-    p->colwaves_d[d] = colwaves;
+    p->colwaves_d[d] = colwaves > 0 ? colwaves : eight ? 2 | stage : 1;
   }
   p->rows_d[0] = 0;         // dimension 0: automatic form
   const int64_t o2 = (int64_t)p->o * p->o;

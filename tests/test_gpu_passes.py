@@ -274,3 +274,16 @@ def test_pair_of_many_cells_costs_no_more_than_the_sweeps(sl, k, tier, amp):
         t.append(_time(plan, seq, 4, a, b))
     assert t[1] <= 1.4 * t[0], t
     plan.close()
+
+
+@pytest.mark.parametrize("ns,k,tier,want", [
+    ((1024, 8, 10, 10), 3, "bf16", [(4, 1), (4, 1), (4, 1)]),     # 10 rows fill 8 + 2
+    ((64, 64, 64, 3), 2, "bf16", [(8, 2), (8, 2), (4, 1)]),
+    ((48, 48, 48, 48), 2, "bf16", [(8, 18)] * 3), ((48, 48, 48, 48), 2, "fp32", [(8, 2)] * 3),
+    ((32, 32, 32, 27), 1, "fp16", [(8, 2), (8, 2), (4, 1)]),
+    ((32, 32, 32, 27), 2, "fp16", [(8, 2)] * 3),
+    ((24, 24, 24, 24), 2, "fp32", [(4, 1)] * 3), ((96, 96, 96), 2, "fp32", [(4, 1)] * 2)])
+def test_default_shapes_of_uneven_grids(sl, ns, k, tier, want):
+    plan = sl.Plan(ns, k, tier)
+    assert [(s["rows"], s["colwaves"]) for s in plan.shapes()[1:]] == want
+    plan.close()
