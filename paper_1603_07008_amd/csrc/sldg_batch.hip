@@ -597,15 +597,24 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
     if (e != hipSuccess)
       return drop_sequence(fail(SLDG_ERR_NOMEM, "batch tables: %s", hipGetErrorString(e)));
   }
-  // every table, in one launch per degree
-  std::vector<TableJob> jobs[3];
-  int64_t nblk[3] = {0, 0, 0};
+  // every table, kTableJobs to a launch of one degree
+  TableJobs jobs[3];
+  for (int c = 0; c < 3; ++c) jobs[c] = TableJobs{};
+  auto flush = [&](int c) {
+    const hipError_t r = jobs[c].count ? launch_line_tables_jobs(c + 1, jobs[c], b->stream) : hipSuccess;
+    jobs[c] = TableJobs{};
+    return r;
+  };
   auto add = [&](int q, int p, double* ab, bool em) {
+    if (e != hipSuccess) return;
     const size_t i = (size_t)q * b->nprob + p;
     const int c = b->k[p] - 1;
-    jobs[c].push_back({shifts[i], b->d_s + b->tab_off[i], ab, (int32_t)b->tab_n[i],
-                       (int32_t)ext(b, p)[dims[q]], em ? 1 : 0, (int32_t)nblk[c]});
-    nblk[c] += (b->tab_n[i] + 255) / 256;
+    const int64_t blocks = (b->tab_n[i] + 255) / 256;
+    if (jobs[c].count == kTableJobs || jobs[c].blocks + blocks > 0x7fffffff) e = flush(c);
+    TableJob& j = jobs[c].job[jobs[c].count++];
+    j = {shifts[i], b->d_s + b->tab_off[i], ab, (int32_t)b->tab_n[i],
+         (int32_t)ext(b, p)[dims[q]], em ? 1 : 0, (int32_t)jobs[c].blocks};
+    jobs[c].blocks += blocks;
   };
   for (int q = 0; q < nseq; ++q)
     for (int p = 0; p < b->nprob; ++p) {
@@ -615,20 +624,8 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
       add(q, p, b->d_em + pi.ab0, true);
       if (pi.ab1 != pi.ab0) add(q + 2, p, b->d_em + pi.ab1, true);
     }
-  for (int c = 0; c < 3; ++c) {
-    if (jobs[c].empty()) continue;
-    if (nblk[c] > 0x7fffffff) return drop_sequence(fail(SLDG_ERR_UNSUPPORTED, "batch tables too long"));
-    TableJob* d = nullptr;
-    e = dev_malloc(&d, sizeof(TableJob) * jobs[c].size());
-    if (e != hipSuccess)
-      return drop_sequence(fail(SLDG_ERR_NOMEM, "batch tables: %s", hipGetErrorString(e)));
-    e = hipMemcpy(d, jobs[c].data(), sizeof(TableJob) * jobs[c].size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-      e = launch_line_tables_jobs(c + 1, d, (int32_t)jobs[c].size(), (int32_t)nblk[c], b->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);   // before the list is freed
-    dev_free(d);
-    if (e != hipSuccess) return drop_sequence(device_error(e, "batch line tables"));
-  }
+  for (int c = 0; c < 3 && e == hipSuccess; ++c) e = flush(c);
+  if (e != hipSuccess) return drop_sequence(device_error(e, "batch line tables"));
   b->rows.assign((size_t)nseq * kClasses, 4);
   b->tuples.assign((size_t)nseq * kClasses, 9);
   b->tuned_ms.assign((size_t)nseq * kClasses, -1.0);

@@ -137,16 +137,21 @@ hipError_t launch_line_tables(int k, int64_t n, int64_t period, const double* si
                               bool adjoint, hipStream_t st);
 hipError_t launch_line_tables_set(int k, const TableSet& set, int32_t* s_out, double* ab_out,
                                   hipStream_t st);
-// The tables of one sweep of one problem among many of the same degree (device
-// array): n entries in the blocks from blk0 on, 256 each.
+// The tables of one sweep of one problem among many of the same degree: n entries
+// in the blocks from blk0 on, 256 each.
 struct TableJob {
   const double* sigma;
   int32_t* s;
   double* ab;
   int32_t n, period, entry_major, blk0;
 };
-hipError_t launch_line_tables_jobs(int k, const TableJob* jobs, int32_t njobs, int32_t nblocks,
-                                   hipStream_t st);
+constexpr int32_t kTableJobs = 64;             // in a launch's arguments
+struct TableJobs {
+  int32_t count;
+  int64_t blocks;
+  TableJob job[kTableJobs];
+};
+hipError_t launch_line_tables_jobs(int k, const TableJobs& jobs, hipStream_t st);
 hipError_t launch_sweep(int k, int tier, int dim, const SweepArgs& a, hipStream_t st);
 hipError_t launch_mass(const double* mass, int64_t n, double* partial, int nblocks,
                        double* result, hipStream_t st);

@@ -173,18 +173,18 @@ __global__ __launch_bounds__(256) void line_tables_set_kernel(TableSet set,
     line_table_component<K, false>((int)blockIdx.y, sg, set.period[q], s_out + t, ab, em ? 1 : n);
 }
 
-// The tables of any number of sweeps (a batch): job i takes the blocks from
-// blk0 on, 256 entries each.
+// The tables of many sweeps (a batch): job i takes the blocks from blk0 on, 256
+// entries each.  The jobs are kernel arguments: a list in device memory would need
+// an allocation, and a wait for the stream before it is freed.
 template <int K>
-__global__ __launch_bounds__(256) void line_tables_jobs_kernel(const TableJob* __restrict__ jobs,
-                                                               int32_t njobs) {
-  int32_t lo = 0, hi = njobs - 1;                  // the last job with blk0 <= blockIdx.x
+__global__ __launch_bounds__(256) void line_tables_jobs_kernel(TableJobs jobs) {
+  int32_t lo = 0, hi = jobs.count - 1;             // the last job with blk0 <= blockIdx.x
   while (lo < hi) {
     const int32_t mid = (lo + hi + 1) >> 1;
-    if (jobs[mid].blk0 <= (int32_t)blockIdx.x) lo = mid;
+    if (jobs.job[mid].blk0 <= (int32_t)blockIdx.x) lo = mid;
     else hi = mid - 1;
   }
-  const TableJob j = jobs[lo];
+  const TableJob j = jobs.job[lo];
   const int64_t t = (int64_t)((int32_t)blockIdx.x - j.blk0) * 256 + threadIdx.x;
   if (t >= j.n) return;
   constexpr int64_t E = 2LL * (K + 1) * (K + 1);
@@ -229,14 +229,13 @@ hipError_t launch_line_tables_set(int k, const TableSet& set, int32_t* s_out, do
   return hipGetLastError();
 }
 
-hipError_t launch_line_tables_jobs(int k, const TableJob* jobs, int32_t njobs, int32_t nblocks,
-                                   hipStream_t st) {
-  if (njobs <= 0 || nblocks <= 0) return hipSuccess;
-  dim3 grid((unsigned)nblocks, table_components(k)), block(256);
+hipError_t launch_line_tables_jobs(int k, const TableJobs& jobs, hipStream_t st) {
+  if (jobs.blocks <= 0) return hipSuccess;
+  dim3 grid((unsigned)jobs.blocks, table_components(k)), block(256);
   switch (k) {
-    case 1: line_tables_jobs_kernel<1><<<grid, block, 0, st>>>(jobs, njobs); break;
-    case 2: line_tables_jobs_kernel<2><<<grid, block, 0, st>>>(jobs, njobs); break;
-    case 3: line_tables_jobs_kernel<3><<<grid, block, 0, st>>>(jobs, njobs); break;
+    case 1: line_tables_jobs_kernel<1><<<grid, block, 0, st>>>(jobs); break;
+    case 2: line_tables_jobs_kernel<2><<<grid, block, 0, st>>>(jobs); break;
+    case 3: line_tables_jobs_kernel<3><<<grid, block, 0, st>>>(jobs); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
