@@ -571,23 +571,28 @@ sldg_status sldg_batch_bind(sldg_batch_t batch, double* const* mass0, void* cons
  * step); set the sequence again after changing displacements. */
 sldg_status sldg_batch_set_sequence(sldg_batch_t batch, int nseq, const int* dims,
                                     const uint32_t* masks, const double* const* shifts);
-/* nsteps split steps; sweep number q (over all steps) reads buffer q % 2 and
- * writes the other; *result_buffer receives the buffer holding the result.
+/* nsteps split steps; *result_buffer receives the buffer holding the result,
+ * (nsteps * nseq) % 2.  Sweeps along 0, 1, 0 in a row run as one X V X pass, bitwise
+ * the three sweeps, of the problems it pays for (the others' sweeps run one by
+ * one beside it); other sweeps read one buffer and write the other in turn.
  * use_graph != 0: each step is captured once (per starting buffer) into a
  * HIP graph and replayed. */
 sldg_status sldg_batch_run(sldg_batch_t batch, int nsteps, int use_graph, int* result_buffer);
 /* Launch-shape tuner: for every sweep of the sequence and every class of its
- * work list (tile kind: 0 dimension-0 window form, 1 dimension-0 group form,
+ * work list (the problems that run the sweep by itself, none where all run it in an
+ * X V X pass; tile kind: 0 dimension-0 window form, 1 dimension-0 group form,
  * 2 strided; x degree 1..3; class = 3 * kind + k - 1), times rows-per-thread
  * {2, 4, 8, 0} (strided sweeps; 0 the lane form, one cell per lane) or {4, 1}
  * (dimension 0: the group form, or with rows 1 the lane form; the window form
  * ignores rows) x
  * tuples-per-thread {1, 3, 9, all} on the bound data (reads buffer 0,
- * overwrites buffer 1) and keeps the fastest per class. */
+ * overwrites buffer 1) and keeps the fastest per class; for every X V X pass rows
+ * per strip {4, 8, 16}. */
 sldg_status sldg_batch_tune(sldg_batch_t batch, int reps);
 /* Set the launch shape of every class of sweep q (rows 2, 4 or 8; the lane
- * form: 1 along dimension 0, 0 along others; tuples 0 = all).  get: the shape of the class with the most tiles, and the tuned
- * time of the whole sweep (-1 if not tuned). */
+ * form: 1 along dimension 0, 0 along others; tuples 0 = all).  get: the shape of the
+ * class with the most tiles, and the tuned time of the whole sweep (-1 if not
+ * tuned), a third of the pass's for a sweep that runs in an X V X pass. */
 sldg_status sldg_batch_get_tuning(sldg_batch_t batch, int q, int* rows, int* tuples, double* ms);
 sldg_status sldg_batch_set_tuning(sldg_batch_t batch, int q, int rows, int tuples);
 /* Shape, tuned time (ms, -1 if not tuned) and tile count of class `cls` (0..8)
@@ -596,6 +601,12 @@ sldg_status sldg_batch_get_class_tuning(sldg_batch_t batch, int q, int cls, int*
                                         int* tuples, double* ms, int* nitems);
 /* Set the launch shape of class `cls` of sweep q alone. */
 sldg_status sldg_batch_set_class_tuning(sldg_batch_t batch, int q, int cls, int rows, int tuples);
+/* Rows per strip, tuned time (ms, -1 if not tuned) and tile count of the X V X pass
+ * that starts at sweep q (0, -1, 0 where none does).  set: rows 4, 8 or 16, or 0 for
+ * the library's choice (kept, without effect, where no pass starts). */
+sldg_status sldg_batch_get_pass_tuning(sldg_batch_t batch, int q, int* rows, double* ms,
+                                       int* nitems);
+sldg_status sldg_batch_set_pass_tuning(sldg_batch_t batch, int q, int rows);
 
 /*
  * Device memory the library allocates for itself: plan tables, the scaled

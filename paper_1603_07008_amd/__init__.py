@@ -34,7 +34,8 @@ EXPORTS = ("sldg_plan", "sldg_plan_destroy", "sldg_plan_set_stream", "sldg_line_
            "sldg_poisson_shift", "sldg_poisson_shift_noalloc", "sldg_vlasov_poisson_steps",
            "sldg_advect_dim_collocated", "sldg_poisson_shift_2d", "sldg_vlasov_poisson_steps_2d2v",
            "sldg_set_device_alloc_limit", "sldg_device_alloc_bytes", "sldg_advect_dims01",
-           "sldg_plan_set_fusion", "sldg_split_steps_adjoint")
+           "sldg_plan_set_fusion", "sldg_split_steps_adjoint", "sldg_batch_get_pass_tuning",
+           "sldg_batch_set_pass_tuning")
 
 
 class SldgError(RuntimeError):

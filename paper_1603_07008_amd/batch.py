@@ -50,6 +50,12 @@ def _lib():
         L.sldg_batch_get_class_tuning.restype = i32
         L.sldg_batch_set_class_tuning.argtypes = [vp, i32, i32, i32, i32]
         L.sldg_batch_set_class_tuning.restype = i32
+        L.sldg_batch_get_pass_tuning.argtypes = [vp, i32, ctypes.POINTER(i32),
+                                                 ctypes.POINTER(ctypes.c_double),
+                                                 ctypes.POINTER(i32)]
+        L.sldg_batch_get_pass_tuning.restype = i32
+        L.sldg_batch_set_pass_tuning.argtypes = [vp, i32, i32]
+        L.sldg_batch_set_pass_tuning.restype = i32
         _bound = True
     return L
 
@@ -178,7 +184,8 @@ class Batch:
 
     def tuning(self):
         """Per sweep: the shape of its largest class, the tuned time of the
-        sweep, and the shape, time and tile count of every non-empty class."""
+        sweep, and the shape, time and tile count of every non-empty class;
+        "pass" where an X V X pass starts: its rows per strip, time and tiles."""
         out = []
         for q in range(self.nseq):
             r, t, ms = ctypes.c_int(), ctypes.c_int(), ctypes.c_double()
@@ -194,7 +201,14 @@ class Batch:
                 if n.value:
                     classes[str(c)] = {"rows": cr.value, "tuples": ct.value, "ms": cms.value,
                                        "tiles": n.value}
-            out.append({"rows": r.value, "tuples": t.value, "ms": ms.value, "classes": classes})
+            sweep = {"rows": r.value, "tuples": t.value, "ms": ms.value, "classes": classes}
+            pr, pms, n = ctypes.c_int(), ctypes.c_double(), ctypes.c_int()
+            _check(_lib().sldg_batch_get_pass_tuning(self.handle, q, ctypes.byref(pr),
+                                                     ctypes.byref(pms), ctypes.byref(n)),
+                   "sldg_batch_get_pass_tuning")
+            if pr.value:
+                sweep["pass"] = {"rows": pr.value, "ms": pms.value, "tiles": n.value}
+            out.append(sweep)
         return out
 
     def set_class_tuning(self, q, cls, rows, tuples):
@@ -203,8 +217,14 @@ class Batch:
         _check(_lib().sldg_batch_set_class_tuning(self.handle, int(q), int(cls), int(rows),
                                                   int(tuples)), "sldg_batch_set_class_tuning")
 
+    def set_pass_tuning(self, q, rows):
+        """Rows per strip of the X V X pass that starts at sweep q
+        (sldg_batch_set_pass_tuning)."""
+        _check(_lib().sldg_batch_set_pass_tuning(self.handle, int(q), int(rows)),
+               "sldg_batch_set_pass_tuning")
+
     def set_tuning(self, shapes):
-        """Apply shapes as `tuning()` returns them (per class when given)."""
+        """Apply shapes as `tuning()` returns them (per class and pass when given)."""
         for q, sh in enumerate(shapes):
             _check(_lib().sldg_batch_set_tuning(self.handle, q, int(sh["rows"]), int(sh["tuples"])),
                    "sldg_batch_set_tuning")
@@ -212,6 +232,8 @@ class Batch:
                 _check(_lib().sldg_batch_set_class_tuning(self.handle, q, int(c), int(cs["rows"]),
                                                           int(cs["tuples"])),
                        "sldg_batch_set_class_tuning")
+            if "pass" in sh:
+                self.set_pass_tuning(q, sh["pass"]["rows"])
 
     def tune_cached(self, path, reps=3):
         """Tuned shapes from the JSON cache at `path` if it has this batch's

@@ -20,14 +20,6 @@
 
 using namespace sldg;
 
-// A problem's part in an X V X pass (sweeps q, q + 1, q + 2 along dimensions
-// 0, 1, 0; sldg_strang.h): whether the pass takes it, and where the
-// entry-major matrices of its two X sweeps are.
-struct PassInfo {
-  bool on = false;
-  int64_t ab0 = 0, ab1 = 0;
-};
-
 struct sldg_batch_s {
   int nprob = 0, ndim = 0;
   sldg_tier tier = SLDG_TIER_FP64;
@@ -56,17 +48,18 @@ struct sldg_batch_s {
   std::vector<BatchItem*> d_items;
   std::vector<int32_t> nitems;
   std::vector<int32_t> cls_off;           // [nseq * (kClasses + 1)] class offsets in the list
-  // X V X passes: per first sweep q the problems taken, their arguments and
-  // items (by degree), and the work lists of the
-  // problems that run sweep by sweep
+  // X V X passes (sweeps q, q + 1, q + 2 along dimensions 0, 1, 0; sldg_strang.h):
+  // per first sweep q the problems taken, their arguments and items (by degree).
+  // The work lists above hold the other problems; the matrices of a taken
+  // problem's X sweeps are entry-major, in the place of component-major ones.
   std::vector<char> triple;               // [nseq] a pass starts here
-  std::vector<PassInfo> pass;             // [nseq * nprob]
-  double* d_em = nullptr;                 // entry-major matrices of the passes' X sweeps
+  std::vector<char> pass;                 // [nseq * nprob] at q: the pass takes the problem
+                                          // (2: with one table for both its X sweeps)
   std::vector<StrangArgs*> d_pass_args;   // [nseq * 2]
   std::vector<BatchItem*> d_pass_items;   // [nseq]
   std::vector<int32_t> pass_off;          // [nseq * (kPassClasses + 1)]
-  std::vector<BatchItem*> d_rest;         // [nseq]
-  std::vector<int32_t> rest_off;          // [nseq * (kClasses + 1)]
+  std::vector<int> pass_rows;             // [nseq] rows per strip (0: by rule), as tuned
+  std::vector<double> pass_ms;            // [nseq] tuned time (-1: not tuned)
   bool ready = false;
   hipGraphExec_t graph[2] = {nullptr, nullptr};
 };
@@ -116,12 +109,9 @@ void free_work(sldg_batch_s* b) {
   for (auto* p : b->d_items) if (p) dev_free(p);
   for (auto* p : b->d_pass_args) if (p) dev_free(p);
   for (auto* p : b->d_pass_items) if (p) dev_free(p);
-  for (auto* p : b->d_rest) if (p) dev_free(p);
   b->d_pass_args.clear();
   b->d_pass_items.clear();
   b->pass_off.clear();
-  b->d_rest.clear();
-  b->rest_off.clear();
   b->d_args.clear();
   b->d_items.clear();
   b->nitems.clear();
@@ -135,7 +125,6 @@ void free_batch(sldg_batch_s* b) {
   free_work(b);
   if (b->d_s) dev_free(b->d_s);
   if (b->d_ab) dev_free(b->d_ab);
-  if (b->d_em) dev_free(b->d_em);
   if (b->d_pmap) dev_free(b->d_pmap);
   delete b;
 }
@@ -163,13 +152,28 @@ sldg_status upload_items(BatchItem*& d, const std::vector<BatchItem>& items, con
   return e == hipSuccess ? SLDG_OK : device_error(e, what);
 }
 
-// Build the device argument blocks and work list of sweep q.
+// Whether problem p runs sweep q in an X V X pass.
+bool in_pass(const sldg_batch_s* b, int q, int p) {
+  const int first = triple_of(b, q);
+  return first >= 0 && b->pass[(size_t)first * b->nprob + p];
+}
+
+// Before arguments and lists that exist are written anew: launches that read them
+// may be under way, and the copies below do not wait for the batch's stream.
+sldg_status wait_for_launches(const sldg_batch_s* b, bool exist) {
+  const hipError_t e = exist ? hipStreamSynchronize(b->stream) : hipSuccess;
+  return e == hipSuccess ? SLDG_OK : device_error(e, "batch rebuild");
+}
+
+// Build the device argument blocks and work list of sweep q, of the problems no
+// X V X pass takes.
 sldg_status build_sweep_impl(sldg_batch_s* b, int q) {
   const int dim = b->dims[q];
   std::vector<SweepArgs> args[2];
   std::vector<BatchItem> bucket[kClasses];
   for (int s = 0; s < 2; ++s) args[s].resize(b->nprob);
   for (int p = 0; p < b->nprob; ++p) {
+    if (in_pass(b, q, p)) continue;
     const int o = b->k[p] + 1;
     const uint32_t mask = b->masks[(size_t)q * b->nprob + p];
     // the problem's class: tile kind (window needs N_0 % 4 == 0 and aligned buffers) x degree
@@ -233,26 +237,20 @@ sldg_status build_sweep_impl(sldg_batch_s* b, int q) {
           for (int64_t x = 0; x < xt; ++x) bk.push_back({p, 2, (int32_t)x, qg, (int32_t)z});
     }
   }
-  std::vector<BatchItem> items, rest;
-  std::vector<int32_t> off(kClasses + 1, 0), roff(kClasses + 1, 0);
-  const int first = triple_of(b, q);
+  std::vector<BatchItem> items;
+  std::vector<int32_t> off(kClasses + 1, 0);
   for (int c = 0; c < kClasses; ++c) {
     off[c] = (int32_t)std::min<size_t>(items.size(), 0x7fffffff);
-    roff[c] = (int32_t)std::min<size_t>(rest.size(), 0x7fffffff);
     items.insert(items.end(), bucket[c].begin(), bucket[c].end());
-    if (first >= 0)
-      for (const BatchItem& w : bucket[c])
-        if (!b->pass[(size_t)first * b->nprob + w.prob].on) rest.push_back(w);
     if (bucket[c].size() > 0x7fffffff || items.size() > 0x7fffffff)
       return fail(SLDG_ERR_UNSUPPORTED, "work list too long");
   }
   off[kClasses] = (int32_t)items.size();
-  roff[kClasses] = (int32_t)rest.size();
   b->cls_off.resize((size_t)b->nseq * (kClasses + 1));
   std::copy(off.begin(), off.end(), b->cls_off.begin() + (size_t)q * (kClasses + 1));
-  b->rest_off.resize((size_t)b->nseq * (kClasses + 1));
-  std::copy(roff.begin(), roff.end(), b->rest_off.begin() + (size_t)q * (kClasses + 1));
-  for (int s = 0; s < 2; ++s) {
+  sldg_status st = wait_for_launches(b, b->d_args[(size_t)q * 2] || b->d_items[q]);
+  if (st != SLDG_OK) return st;
+  for (int s = 0; s < 2 && !items.empty(); ++s) {
     SweepArgs*& d = b->d_args[(size_t)q * 2 + s];
     if (!d) {
       hipError_t e = dev_malloc(&d, sizeof(SweepArgs) * b->nprob);
@@ -261,24 +259,41 @@ sldg_status build_sweep_impl(sldg_batch_s* b, int q) {
     hipError_t e = hipMemcpy(d, args[s].data(), sizeof(SweepArgs) * b->nprob, hipMemcpyHostToDevice);
     if (e != hipSuccess) return device_error(e, "batch arguments upload");
   }
-  sldg_status st = upload_items(b->d_items[q], items, "batch work list");
-  if (st == SLDG_OK) st = upload_items(b->d_rest[q], rest, "batch work list");
+  st = upload_items(b->d_items[q], items, "batch work list");
   if (st != SLDG_OK) return st;
   b->nitems[q] = (int32_t)items.size();
   return SLDG_OK;
 }
 
-// Rows per strip of the X V X pass.  A strip loads and X-sweeps three rows
-// more than it has, so 16 rows where that leaves the chip enough waves, else 8
-// (measured on 512 problems of 32-512 cells a side, 50,000 strips of 16: 1.92
-// ms for two steps with 16 rows, 1.89 with 8, 2.01 with 24; on 40 of them,
-// 4,000 strips: 0.220 ms with 16 rows, 0.196 with 8).
+// Rows per strip of the X V X pass.  A strip loads and X-sweeps three rows more
+// than it has; 8 rows but for the 16-bit tiers, whose waves are short, on batches of
+// 16,384 strips of 16 on.  Measured (us a step with 4, 8, 16 rows): 512 problems of
+// 32-512 cells a side, 43,000 strips, FP32 991, 914, 937, BF16 824, 735, 711, FP64
+// 1548, 1431, 1449; 200 of them 443, 417, 426 and 374, 343, 343; 40 of them 121, 118,
+// 127 and 97, 101, 111; 100 of 32-128 cells, 960 strips, FP32 51, 58, 82 (the tuner
+// finds 4).
 int32_t pass_rows(const sldg_batch_s* b, int q) {
+  if (b->pass_rows[(size_t)q] > 0) return b->pass_rows[(size_t)q];
   int64_t strips = 0;
   for (int p = 0; p < b->nprob; ++p)
-    if (b->pass[(size_t)q * b->nprob + p].on)
+    if (b->pass[(size_t)q * b->nprob + p])
       strips += ((ext(b, p)[0] + 61) / 62) * ((ext(b, p)[1] + 15) / 16);
-  return strips >= 16384 ? 16 : 8;
+  return strips >= 16384 && elem_size(b->tier) == 2 ? 16 : 8;
+}
+
+// Device bytes of the arguments and lists of sweeps q, q + 1, q + 2 one by one, of
+// every problem or (rest) of those the pass at q leaves, with 4 rows and 9 tuples a
+// thread; dimension 0 in the window form, whose tiles are the fewest.
+int64_t sweep_bytes(const sldg_batch_s* b, int q, bool rest = false) {
+  int64_t items = 0;
+  for (int p = 0; p < b->nprob; ++p) {
+    if (rest && b->pass[(size_t)q * b->nprob + p]) continue;
+    const int64_t nspec = b->modes[p] / (b->k[p] + 1), runs = (nspec + 8) / 9;
+    const int64_t N1 = ext(b, p)[1];
+    items += 2 * runs * ((b->cells[p] / 4 + 255) / 256);
+    items += runs * ((b->cells[p] / N1 + 63) / 64) * (((N1 + 3) / 4 + 3) / 4);
+  }
+  return (int64_t)sizeof(BatchItem) * items + (int64_t)sizeof(SweepArgs) * 6 * b->nprob;
 }
 
 // Device arguments and work list of the X V X pass that starts at sweep q.
@@ -288,8 +303,7 @@ sldg_status build_pass(sldg_batch_s* b, int q) {
   std::vector<BatchItem> bucket[kPassClasses];
   for (int s = 0; s < 2; ++s) args[s].resize(b->nprob);
   for (int p = 0; p < b->nprob; ++p) {
-    const PassInfo& pi = b->pass[(size_t)q * b->nprob + p];
-    if (!pi.on) continue;
+    if (!b->pass[(size_t)q * b->nprob + p]) continue;
     const int k = b->k[p], o = k + 1;
     const int64_t* n = ext(b, p);
     StrangArgs x{};
@@ -306,8 +320,8 @@ sldg_status build_pass(sldg_batch_s* b, int q) {
       SweepArgs a{};
       int64_t nt = 0;
       describe_grid(b->ndim, n, o, b->modes[p], i == 1 ? 1 : 0, b->masks[at], 4, 0, a, nt);
-      const double* ab = i == 1 ? b->d_ab + b->ab_off[at] : b->d_em + (i == 0 ? pi.ab0 : pi.ab1);
-      *tab[i] = {b->d_s + b->tab_off[at], ab, i == 1 ? nt : 1, i == 1 ? 1 : 2LL * o * o,
+      const size_t tb = i == 2 && b->pass[(size_t)q * b->nprob + p] == 2 ? at - 2 * (size_t)b->nprob : at;
+      *tab[i] = {b->d_s + b->tab_off[tb], b->d_ab + b->ab_off[tb], i == 1 ? nt : 1, i == 1 ? 1 : 2LL * o * o,
                  (int32_t)(b->masks[at] >> (i == 1 ? 0 : 1) & 1), a.map};
     }
     for (int src = 0; src < 2; ++src) {
@@ -333,6 +347,8 @@ sldg_status build_pass(sldg_batch_s* b, int q) {
     if (items.size() > 0x7fffffff) return fail(SLDG_ERR_UNSUPPORTED, "work list too long");
   }
   off[kPassClasses] = (int32_t)items.size();
+  sldg_status st = wait_for_launches(b, b->d_pass_args[(size_t)q * 2] || b->d_pass_items[q]);
+  if (st != SLDG_OK) return st;
   for (int s = 0; s < 2 && !items.empty(); ++s) {
     StrangArgs*& d = b->d_pass_args[(size_t)q * 2 + s];
     hipError_t e = d ? hipSuccess : dev_malloc(&d, sizeof(StrangArgs) * b->nprob);
@@ -343,10 +359,40 @@ sldg_status build_pass(sldg_batch_s* b, int q) {
   return upload_items(b->d_pass_items[q], items, "batch work list");
 }
 
+// Device bytes of the lists and arguments of sweeps q, q + 1, q + 2: with the pass
+// that starts at q, and (at most) with every problem sweep by sweep in the shapes
+// of a new sequence.
+int64_t pass_bytes(const sldg_batch_s* b, int q) {
+  const int32_t rows = pass_rows(b, q);
+  int64_t items = 0;
+  bool rest = false;
+  for (int p = 0; p < b->nprob; ++p) {
+    if (!b->pass[(size_t)q * b->nprob + p]) {
+      rest = true;
+      continue;
+    }
+    StrangArgs x{};
+    x.N0 = (int32_t)ext(b, p)[0];
+    x.N1 = (int32_t)ext(b, p)[1];
+    strang_tiles(x, rows);
+    const int o = b->k[p] + 1;
+    items += (int64_t)x.ntile * x.nstrip * (b->cells[p] / ((int64_t)x.N0 * x.N1)) * (b->modes[p] / (o * o));
+  }
+  return (int64_t)sizeof(BatchItem) * items + (int64_t)sizeof(StrangArgs) * 2 * b->nprob +
+         (rest ? sweep_bytes(b, q, true) : 0);
+}
+
 // A sweep whose work list could not be built leaves the batch not ready (run
 // refuses) until the states or the sequence are set again.
 sldg_status build_sweep(sldg_batch_s* b, int q) {
   const sldg_status st = build_sweep_impl(b, q);
+  if (st != SLDG_OK) b->ready = false;
+  return st;
+}
+
+// ... and the same for a pass.
+sldg_status rebuild_pass(sldg_batch_s* b, int q) {
+  sldg_status st = build_pass(b, q);
   if (st != SLDG_OK) b->ready = false;
   return st;
 }
@@ -358,7 +404,6 @@ sldg_status build_all(sldg_batch_s* b) {
   b->d_args.resize((size_t)b->nseq * 2, nullptr);
   b->d_items.resize(b->nseq, nullptr);
   b->nitems.resize(b->nseq, 0);
-  b->d_rest.resize(b->nseq, nullptr);
   b->d_pass_args.resize((size_t)b->nseq * 2, nullptr);
   b->d_pass_items.resize(b->nseq, nullptr);
   for (int q = 0; q < b->nseq; ++q) {
@@ -370,18 +415,31 @@ sldg_status build_all(sldg_batch_s* b) {
   return SLDG_OK;
 }
 
-// One sweep: of every problem, or (rest) of those no X V X pass takes.
-sldg_status launch(sldg_batch_s* b, int q, int src, bool rest = false) {
-  const int32_t* off = (rest ? b->rest_off : b->cls_off).data() + (size_t)q * (kClasses + 1);
-  const BatchItem* list = rest ? b->d_rest[q] : b->d_items[q];
+// One sweep of the problems no X V X pass takes.
+sldg_status launch(sldg_batch_s* b, int q, int src) {
+  const int32_t* off = b->cls_off.data() + (size_t)q * (kClasses + 1);
   for (int c = 0; c < kClasses; ++c) {
     const int32_t n = off[c + 1] - off[c];
     if (n <= 0) continue;
     const int kind = c / 3, k = c % 3 + 1;
     hipError_t e = launch_batch_class((int)b->tier, k, kind, b->rows[(size_t)q * kClasses + c],
-                                      b->d_args[(size_t)q * 2 + src], list + off[c], n,
+                                      b->d_args[(size_t)q * 2 + src], b->d_items[q] + off[c], n,
                                       xcd_group(kind == 2), b->stream);
     if (e != hipSuccess) return device_error(e, "batched sweep launch");
+  }
+  return SLDG_OK;
+}
+
+// The X V X pass that starts at sweep q.
+sldg_status launch_pass(sldg_batch_s* b, int q, int src) {
+  const int32_t* off = b->pass_off.data() + (size_t)q * (kPassClasses + 1);
+  for (int c = kPassClasses - 1; c >= 0; --c) {
+    const int32_t n = off[c + 1] - off[c];
+    if (n <= 0) continue;
+    const hipError_t e =
+        launch_batch_strang(c + 1, (int)b->tier, b->d_pass_args[(size_t)q * 2 + src],
+                            b->d_pass_items[q] + off[c], n, kXcdPass, b->stream);
+    if (e != hipSuccess) return device_error(e, "batched X V X launch");
   }
   return SLDG_OK;
 }
@@ -392,17 +450,9 @@ sldg_status launch_step(sldg_batch_s* b, int& cur) {
   for (int q = 0; q < b->nseq; ++q) {
     sldg_status st = SLDG_OK;
     if (b->triple[(size_t)q]) {
-      const int32_t* off = b->pass_off.data() + (size_t)q * (kPassClasses + 1);
-      for (int c = kPassClasses - 1; c >= 0; --c) {
-        const int32_t n = off[c + 1] - off[c];
-        if (n <= 0) continue;
-        const hipError_t e =
-            launch_batch_strang(c + 1, (int)b->tier, b->d_pass_args[(size_t)q * 2 + cur],
-                                b->d_pass_items[q] + off[c], n, kXcdPass, b->stream);
-        if (e != hipSuccess) return device_error(e, "batched X V X launch");
-      }
+      st = launch_pass(b, q, cur);
       for (int i = 0; i < 3 && st == SLDG_OK; ++i) {
-        st = launch(b, q + i, cur, true);
+        st = launch(b, q + i, cur);
         cur = 1 - cur;
       }
       q += 2;
@@ -525,10 +575,8 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
   free_work(b);
   if (b->d_s) dev_free(b->d_s);
   if (b->d_ab) dev_free(b->d_ab);
-  if (b->d_em) dev_free(b->d_em);
   b->d_s = nullptr;
   b->d_ab = nullptr;
-  b->d_em = nullptr;
   b->nseq = nseq;
   b->dims.assign(dims, dims + nseq);
   b->masks.assign(masks, masks + (size_t)nseq * b->nprob);
@@ -554,21 +602,21 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
   auto drop_sequence = [&](sldg_status st) {
     if (b->d_s) dev_free(b->d_s);
     if (b->d_ab) dev_free(b->d_ab);
-    if (b->d_em) dev_free(b->d_em);
-    b->d_s = nullptr;
+      b->d_s = nullptr;
     b->d_ab = nullptr;
-    b->d_em = nullptr;
-    b->nseq = 0;
+      b->nseq = 0;
     return st;
   };
   hipError_t e = dev_malloc(&b->d_s, sizeof(int32_t) * std::max<int64_t>(1, tot_s));
   if (e == hipSuccess) e = dev_malloc(&b->d_ab, sizeof(double) * std::max<int64_t>(1, tot_ab));
   if (e != hipSuccess)
     return drop_sequence(fail(SLDG_ERR_NOMEM, "batch tables: %s", hipGetErrorString(e)));
-  // X V X passes, and the entry-major matrices of their X sweeps
+  // X V X passes
+  b->pass_rows.assign((size_t)nseq, 0);
+  b->pass_ms.assign((size_t)nseq, -1.0);
   b->triple.assign((size_t)nseq, 0);
-  b->pass.assign((size_t)nseq * b->nprob, PassInfo{});
-  int64_t tot_em = 0, lines = 0;
+  b->pass.assign((size_t)nseq * b->nprob, 0);
+  int64_t lines = 0;
   for (int p = 0; p < b->nprob; ++p)
     lines += (ext(b, p)[0] + 61) / 62 * (b->cells[p] / ext(b, p)[0]) * b->modes[p] /
              ((b->k[p] + 1) * (b->k[p] + 1));
@@ -578,51 +626,37 @@ sldg_status sldg_batch_set_sequence(sldg_batch_t b, int nseq, const int* dims,
       if (!strang_fits(b->cells[p], b->k[p] + 1, elem_size(b->tier)) ||
           !strang_pays(b->k[p], elem_size(b->tier), ext(b, p)[0], lines))
         continue;
-      PassInfo& pi = b->pass[(size_t)q * b->nprob + p];
-      pi.on = true;
+      const size_t i0 = (size_t)q * b->nprob + p, i2 = i0 + 2 * (size_t)b->nprob;
+      b->pass[i0] = shifts[i0] == shifts[i2] && b->masks[i0] == b->masks[i2] ? 2 : 1;
       b->triple[(size_t)q] = 1;
-      const int64_t E = 2LL * (b->k[p] + 1) * (b->k[p] + 1);
-      const size_t i0 = (size_t)q * b->nprob + p, i1 = i0 + 2 * (size_t)b->nprob;
-      pi.ab0 = pi.ab1 = tot_em;
-      tot_em += E * b->tab_n[i0];
-      if (shifts[i0] != shifts[i1] || b->masks[i0] != b->masks[i1]) {
-        pi.ab1 = tot_em;
-        tot_em += E * b->tab_n[i1];
-      }
+    }
+    // under an allocation limit only if its lists take no more than the sweeps'
+    if (b->triple[(size_t)q] && dev_alloc_limited() && pass_bytes(b, q) > sweep_bytes(b, q)) {
+      std::fill_n(b->pass.begin() + (size_t)q * b->nprob, b->nprob, 0);
+      b->triple[(size_t)q] = 0;
     }
     if (b->triple[(size_t)q]) q += 2;
   }
-  if (tot_em > 0) {
-    e = dev_malloc(&b->d_em, sizeof(double) * tot_em);
-    if (e != hipSuccess)
-      return drop_sequence(fail(SLDG_ERR_NOMEM, "batch tables: %s", hipGetErrorString(e)));
-  }
   // every table, kTableJobs to a launch of one degree
   TableJobs jobs[3];
-  for (int c = 0; c < 3; ++c) jobs[c] = TableJobs{};
   auto flush = [&](int c) {
     const hipError_t r = jobs[c].count ? launch_line_tables_jobs(c + 1, jobs[c], b->stream) : hipSuccess;
     jobs[c] = TableJobs{};
     return r;
   };
-  auto add = [&](int q, int p, double* ab, bool em) {
-    if (e != hipSuccess) return;
-    const size_t i = (size_t)q * b->nprob + p;
-    const int c = b->k[p] - 1;
-    const int64_t blocks = (b->tab_n[i] + 255) / 256;
-    if (jobs[c].count == kTableJobs || jobs[c].blocks + blocks > 0x7fffffff) e = flush(c);
-    TableJob& j = jobs[c].job[jobs[c].count++];
-    j = {shifts[i], b->d_s + b->tab_off[i], ab, (int32_t)b->tab_n[i],
-         (int32_t)ext(b, p)[dims[q]], em ? 1 : 0, (int32_t)jobs[c].blocks};
-    jobs[c].blocks += blocks;
-  };
-  for (int q = 0; q < nseq; ++q)
-    for (int p = 0; p < b->nprob; ++p) {
-      add(q, p, b->d_ab + b->ab_off[(size_t)q * b->nprob + p], false);
-      const PassInfo& pi = b->pass[(size_t)q * b->nprob + p];
-      if (!pi.on) continue;
-      add(q, p, b->d_em + pi.ab0, true);
-      if (pi.ab1 != pi.ab0) add(q + 2, p, b->d_em + pi.ab1, true);
+  for (int c = 0; c < 3; ++c) jobs[c] = TableJobs{};
+  for (int q = 0; q < nseq && e == hipSuccess; ++q)
+    for (int p = 0; p < b->nprob && e == hipSuccess; ++p) {
+      const size_t i = (size_t)q * b->nprob + p;
+      if (q >= 2 && b->triple[(size_t)q - 2] && b->pass[i - 2 * (size_t)b->nprob] == 2) continue;
+      const int c = b->k[p] - 1;
+      const int64_t blocks = (b->tab_n[i] + 255) / 256;
+      if (jobs[c].count == kTableJobs || jobs[c].blocks + blocks > 0x7fffffff) e = flush(c);
+      TableJob& j = jobs[c].job[jobs[c].count++];
+      j = {shifts[i], b->d_s + b->tab_off[i], b->d_ab + b->ab_off[i], (int32_t)b->tab_n[i],
+           (int32_t)ext(b, p)[dims[q]], dims[q] == 0 && in_pass(b, q, p) ? 1 : 0,
+           (int32_t)jobs[c].blocks};
+      jobs[c].blocks += blocks;
     }
   for (int c = 0; c < 3 && e == hipSuccess; ++c) e = flush(c);
   if (e != hipSuccess) return drop_sequence(device_error(e, "batch line tables"));
@@ -738,7 +772,8 @@ sldg_status sldg_batch_get_class_tuning(sldg_batch_t b, int q, int cls, int* row
 sldg_status sldg_batch_get_tuning(sldg_batch_t b, int q, int* rows, int* tuples, double* ms) {
   if (!b) return fail(SLDG_ERR_ARG, "batch is NULL");
   if (q < 0 || q >= b->nseq) return fail(SLDG_ERR_ARG, "sweep %d out of range", q);
-  // the shape of the class with the most tiles, and the tuned time of the whole sweep
+  // the shape of the class with the most tiles, and the tuned time of the whole
+  // sweep (of an X V X pass: a third)
   int best = 0;
   int32_t most = -1;
   double tot = 0.0;
@@ -756,10 +791,72 @@ sldg_status sldg_batch_get_tuning(sldg_batch_t b, int q, int* rows, int* tuples,
       else tot += t;
     }
   }
+  const int first = triple_of(b, q);
+  if (first >= 0) {
+    if (b->pass_ms[(size_t)first] < 0) tuned = false;
+    else tot += b->pass_ms[(size_t)first] / 3;
+  }
   if (rows) *rows = b->rows[(size_t)q * kClasses + best];
   if (tuples) *tuples = b->tuples[(size_t)q * kClasses + best];
   if (ms) *ms = tuned ? tot : -1.0;
   return ok();
+}
+
+sldg_status sldg_batch_get_pass_tuning(sldg_batch_t b, int q, int* rows, double* ms, int* nitems) {
+  if (!b) return fail(SLDG_ERR_ARG, "batch is NULL");
+  if (q < 0 || q >= b->nseq) return fail(SLDG_ERR_ARG, "sweep %d out of range", q);
+  const bool on = b->triple[(size_t)q];
+  if (rows) *rows = on ? pass_rows(b, q) : 0;
+  if (ms) *ms = on ? b->pass_ms[(size_t)q] : -1.0;
+  if (nitems)
+    *nitems = on && b->ready ? b->pass_off[(size_t)q * (kPassClasses + 1) + kPassClasses] : 0;
+  return ok();
+}
+
+sldg_status sldg_batch_set_pass_tuning(sldg_batch_t b, int q, int rows) {
+  if (!b) return fail(SLDG_ERR_ARG, "batch is NULL");
+  if (q < 0 || q >= b->nseq) return fail(SLDG_ERR_ARG, "sweep %d out of range", q);
+  if (!(rows == 0 || rows == 4 || rows == 8 || rows == 16))
+    return fail(SLDG_ERR_ARG, "rows %d not in {0, 4, 8, 16}", rows);
+  b->pass_rows[(size_t)q] = rows;
+  b->pass_ms[(size_t)q] = -1.0;
+  if (b->bound && b->triple[(size_t)q]) {
+    drop_graphs(b);
+    sldg_status st = rebuild_pass(b, q);
+    if (st != SLDG_OK) return st;
+  }
+  return ok();
+}
+
+// Times the pass that starts at sweep q with each strip height (under an
+// allocation limit the rule's alone: other lists may not fit) and keeps the
+// fastest.
+static sldg_status tune_pass(sldg_batch_t b, int q, int reps, hipEvent_t e0, hipEvent_t e1) {
+  static const int kRows[3] = {8, 16, 4};
+  const int before = b->pass_rows[(size_t)q];
+  int best_rows = before;
+  double best = 1e300;
+  sldg_status st = SLDG_OK;
+  for (int i = 0; i < (dev_alloc_limited() ? 1 : 3) && st == SLDG_OK; ++i) {
+    b->pass_rows[(size_t)q] = dev_alloc_limited() ? before : kRows[i];
+    st = rebuild_pass(b, q);
+    if (st == SLDG_OK) st = launch_pass(b, q, 0);             // warm-up
+    (void)hipEventRecord(e0, b->stream);
+    for (int r = 0; r < reps && st == SLDG_OK; ++r) st = launch_pass(b, q, 0);
+    (void)hipEventRecord(e1, b->stream);
+    const hipError_t e = hipEventSynchronize(e1);
+    if (st == SLDG_OK && e != hipSuccess) st = device_error(e, "tuning");
+    float ms = 0.f;
+    if (st == SLDG_OK) (void)hipEventElapsedTime(&ms, e0, e1);
+    if (st == SLDG_OK && ms / reps < best) {
+      best = ms / reps;
+      best_rows = b->pass_rows[(size_t)q];
+    }
+  }
+  b->pass_rows[(size_t)q] = best_rows;
+  b->pass_ms[(size_t)q] = best < 1e299 ? best : -1.0;
+  const sldg_status last = rebuild_pass(b, q);
+  return st == SLDG_OK ? last : st;
 }
 
 sldg_status sldg_batch_tune(sldg_batch_t b, int reps) {
@@ -786,7 +883,8 @@ sldg_status sldg_batch_tune(sldg_batch_t b, int reps) {
       best_t[c] = b->tuples[(size_t)q * kClasses + c];
       best[c] = 1e300;
     }
-    const int nr = b->dims[q] == 0 ? 2 : 4;
+    // (a sweep every problem runs in an X V X pass has no launch of its own)
+    const int nr = b->nitems[q] == 0 ? 0 : b->dims[q] == 0 ? 2 : 4;
     for (int ir = 0; ir < nr && st == SLDG_OK; ++ir)
       for (int it = 0; it < 4 && st == SLDG_OK; ++it) {
         // every class of the sweep takes the candidate; each class is timed alone
@@ -829,6 +927,7 @@ sldg_status sldg_batch_tune(sldg_batch_t b, int reps) {
       b->tuned_ms[(size_t)q * kClasses + c] = best[c] < 1e299 ? best[c] : -1.0;
     }
     if (st == SLDG_OK) st = build_sweep(b, q);
+    if (st == SLDG_OK && b->triple[(size_t)q]) st = tune_pass(b, q, reps, ev[0], ev[1]);
   }
   for (int i = 0; i < kClasses + 1; ++i) (void)hipEventDestroy(ev[i]);
   drop_graphs(b);

@@ -171,6 +171,11 @@ bool dev_alloc_fits(int64_t bytes) {
   return g_alloc_limit < 0 || g_alloc_live + bytes <= g_alloc_limit;
 }
 
+bool dev_alloc_limited() {
+  std::lock_guard<std::mutex> lock(g_alloc_mu);
+  return g_alloc_limit >= 0;
+}
+
 void describe_grid(int ndim, const int64_t* n, int o, int64_t modes, int dim, uint32_t dep_mask,
                    int rows_per_thread, int tuples_per_thread, SweepArgs& a, int64_t& ntab) {
   int64_t P = 1, Q = 1, cells = 1;

@@ -275,6 +275,7 @@ hipError_t dev_malloc(T** p, size_t bytes) {
 }
 void dev_free(void* p);
 bool dev_alloc_fits(int64_t bytes);
+bool dev_alloc_limited();                      // whether a limit is set
 
 // Host helpers shared by the plan and batch front ends (sldg_host.hip).
 sldg_status fail(sldg_status st, const char* fmt, ...);

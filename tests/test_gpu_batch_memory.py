@@ -36,6 +36,42 @@ def _batch(grids, dims, seqs, states):
     return b, s0, s1
 
 
+@pytest.mark.parametrize("name", sorted(GRIDS))
+def test_passes_fit_where_the_sweeps_do(sl, name):
+    """The sequence 0, 1, 0 under a limit of what its sweeps need: the bytes of
+    the sequences 0, 1 and 0 (which have no pass) less one empty batch."""
+    import torch
+    grids = GRIDS[name]
+    seqs = [_seq(ns, 2, 1, 2.0, 0.4, i) for i, (ns, _) in enumerate(grids)]
+    plans = [sl.Plan(ns, k, "fp32") for ns, k in grids]
+    states = [_state(p, i) for i, p in enumerate(plans)]
+    held = sl.device_alloc_bytes()
+    need = 0
+    for dims in ((0, 1), (0,)):
+        b, _, _ = _batch(grids, dims, seqs, states)
+        need += sl.device_alloc_bytes() - held
+        b.close()
+    from paper_1603_07008_amd.batch import Batch
+    b = Batch([g[0] for g in grids], [g[1] for g in grids], "fp32")
+    need -= sl.device_alloc_bytes() - held
+    b.close()
+    out = []
+    for limit in (None, held + need):
+        sl.set_device_alloc_limit(limit)
+        try:
+            b, s0, s1 = _batch(grids, (0, 1, 0), seqs, states)
+        finally:
+            sl.set_device_alloc_limit(None)
+        out.append((s0, s1)[b.run(1)])
+        torch.cuda.synchronize()
+        b.close()
+    for x, y in zip(*out):
+        for t, u in zip(x, y):
+            assert torch.equal(_bits(t), _bits(u))
+    for p in plans:
+        p.close()
+
+
 def test_set_sequence_does_not_wait(sl):
     import torch
     from paper_1603_07008_amd.batch import Batch
@@ -74,3 +110,39 @@ def test_more_tables_than_a_launch_holds(sl):
             assert torch.equal(_bits(t), _bits(u)), grids[i]
         p.close()
     b.close()
+
+
+def test_pass_tuning(sl, tmp_path):
+    """The tuner times the launches that run: the pass, no class of its sweeps; its
+    rows change speed, not results, and come back from a cache."""
+    import torch
+    grids = GRIDS["2d"]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        seqs = [_seq(ns, 2, 1, 2.0, 0.4, i) for i, (ns, _) in enumerate(grids)]
+        states = [_state(sl.Plan(ns, k, "fp32"), i) for i, (ns, k) in enumerate(grids)]
+        b, s0, s1 = _batch(grids, (0, 1, 0), seqs, states)
+        ref = None
+        for rows in (0, 4, 8, 16):
+            b.set_pass_tuning(0, rows)
+            for st, init in zip(s0, states):
+                for t, u in zip(st, init):
+                    t.copy_(u)
+            res = b.run(2, use_graph=rows == 8)
+            got = [t.clone() for st in (s0, s1)[res] for t in st]
+            ref = ref or got
+            for t, u in zip(got, ref):
+                assert torch.equal(_bits(t), _bits(u)), rows
+        with pytest.raises(sl.SldgError):
+            b.set_pass_tuning(0, 5)
+        assert "pass" not in b.tuning()[1] and b.tuning()[0]["pass"]["rows"] == 16
+        shapes, cached = b.tune_cached(str(tmp_path / "t.json"))
+        assert not cached
+        assert shapes[0]["pass"]["ms"] > 0 and shapes[0]["pass"]["tiles"] > 0
+        assert all(not s["classes"] for s in shapes)
+        assert abs(sum(s["ms"] for s in shapes) - shapes[0]["pass"]["ms"]) < 1e-9
+        b.set_pass_tuning(0, 0)
+        again, cached = b.tune_cached(str(tmp_path / "t.json"))
+        assert cached and b.tuning()[0]["pass"]["rows"] == shapes[0]["pass"]["rows"]
+        stream.synchronize()
+        b.close()
