@@ -1918,11 +1918,13 @@ sldg_status sldg_vlasov_poisson_steps(sldg_plan_t p, int nsteps, const double* s
   int64_t nblocks = 0;
   const int64_t N0 = p->n[0], N1 = p->n[1];
   const int64_t second = N1;       // tables: the X table by entries, then the one in use
-  if (nsteps > 1 && strang_eligible(p, xs, nblocks) && N1 + std::max(N0, N1) <= p->table_cap) {
+  if (nsteps > 1 && strang_eligible(p, xs, nblocks) && N1 + std::max(N0, N1) <= p->table_cap &&
+      !overlap(shift_x, 8 * N1, shift_v, ob)) {
     // The end of a step and the start of the next, V X X, are one pass; the
     // first X and the last V and X run alone, so that the result lands in the
     // buffer that three sweeps a step leave it in.  The X displacements are
-    // fixed over the call: their table is computed once.
+    // fixed over the call (unless a field solve writes over them): their table
+    // is computed once.
     const int64_t E = 2LL * p->o * p->o;
     auto table = [&](int dim, const double* shift, bool by_entry) -> sldg_status {
       const int64_t at = by_entry ? 0 : second;
@@ -2062,7 +2064,10 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
   // each field solve, where all four fit the plan's table storage together.
   const int64_t o2 = (int64_t)p->o * p->o;
   const int64_t nx = p->n[2] + p->n[3], nv = p->n[0] * p->n[1];
-  const bool tables = nx + 2 * nv <= p->table_cap;
+  bool tables = nx + 2 * nv <= p->table_cap;
+  for (const double* v : {shift_v1, shift_v2})    // (unless a field solve writes over them)
+    if (overlap(shift_x1, 8 * p->n[2], v, ob) || overlap(shift_x2, 8 * p->n[3], v, ob))
+      tables = false;
   int64_t pre[4] = {-1, -1, -1, -1};
   auto compute = [&](int d0, int64_t at) -> sldg_status {
     TableSet set{};

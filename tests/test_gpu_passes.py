@@ -287,3 +287,23 @@ def test_default_shapes_of_uneven_grids(sl, ns, k, tier, want):
     plan = sl.Plan(ns, k, tier)
     assert [(s["rows"], s["colwaves"]) for s in plan.shapes()[1:]] == want
     plan.close()
+
+
+@pytest.mark.parametrize("tier,k", [("fp64", 1), ("fp32", 2), ("bf16", 3), ("fp16", 2)])
+@pytest.mark.parametrize("amp", [0.4, 1.5, 30.0])
+def test_transposed_pair(sl, tier, k, amp):
+    """The transpose of the sweeps d + 1, d is a pair along d, d + 1."""
+    import torch
+    ns = (60, 40, 90)
+    seq = [(2, 1, _uniform(60, amp, 3)), (1, 1, _uniform(60, amp, 4))]
+    _adjoint_both(sl, ns, k, tier, seq, 2)
+    plan = sl.Plan(ns, k, tier)
+    a, b = plan.empty_state(), plan.empty_state()
+    for t in (*a, *b):
+        t.zero_()
+    plan.timing_enable(True)
+    plan.split_steps_adjoint(seq, 2, a, b)
+    assert plan.timing_read(-2)[0] == 2
+    plan.timing_enable(False)
+    torch.cuda.synchronize()
+    plan.close()
