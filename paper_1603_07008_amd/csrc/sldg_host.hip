@@ -659,9 +659,10 @@ sldg_status run_xy(sldg_plan_s* p, const double* shift0, uint32_t mask0, const d
   return timing_end(p, timed, kXYTimingDim);
 }
 
-// Rows per wave of the X V X pass: a wave loads and X-sweeps three rows more
-// than it has, but its rows follow one another, so the most (of 8, 4, 2) that
-// leaves about a wave per SIMD where the grid is small.  Measured (five Strang
+// Rows per wave of the X V X pass: a wave loads four rows more than it has and
+// X-sweeps three more, but its rows follow one another, so the most (of 8, 4, 2, 1)
+// that leaves kStrangWaves waves (of the chip's 1,024 SIMDs) where the grid is
+// small.  Measured (five Strang
 // steps, FP32-mode, rows 1, 2, 4, 8, 16): 256^2 k = 2 (1,280 wave rows) 49, 46,
 // 53, 66, 99 us; 512^2 k = 3 (4,608) 138, 126, 123, 136, 204; 1024^2 k = 3
 // (17,408) 351, 275, 251, 245, 285; 2048^2 k = 3 (69,632) 1414, 1085, 931, 864,
@@ -673,12 +674,14 @@ constexpr int32_t kStrangRows = 8;
 // (sldg_strang.h): at most the cell mean FP64, a spectator group's planes
 // below 2^31 bytes and a launchable grid.  Kernel timing measures the sweeps
 // one by one, so it keeps them apart.
-// The displacements are on the device, so the rule cannot see them: it takes the
-// fields of ordinary steps (up to some cells, a few values over 64 columns;
-// 512^2, k = 2, FP32, shifts to 1.5 cells 15 us a step against 25 for three
-// sweeps, to 3 cells 21).  Wider spreads cost a pass per distinct shift of a
-// wave: to 10 cells over 512 columns 40 us against 26, over 2048 columns 76
-// against 115; sldg_plan_set_fusion turns the pass off.
+// The displacements are on the device, so the rule cannot see them.  Waves of
+// spread V shifts walk each lane's own rows, which on (x, v) grids costs less than
+// the sweeps (512^2, k = 2, FP32: 13 us a step with V shifts to 1.5 cells, 18 to 10,
+// 25 to 30; the sweeps 24) but at k = 3 and 30 cells (42 us against 35).  On
+// full-chip grids of three and more dimensions with short lines it can cost more:
+// 64 x 200 x 32, shifts to 5 cells, k = 2, FP32 96 us against 73, k = 3, BF16 146
+// against 105 (36 against 66 and 84 against 96 below one cell); sldg_plan_set_fusion
+// turns the pass off.
 bool strang_eligible(const sldg_plan_s* p, StrangArgs& x, int64_t& nblocks) {
   if (!p->fuse || p->timing || p->ndim < 2 || p->n_lo > 1) return false;
   const int64_t N0 = p->n[0], N1 = p->n[1];
@@ -785,13 +788,10 @@ bool colpair_eligible(const sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask
          colsweep_tiles(line, (int)p->o, elem_size(p->tier), lds);
 }
 
-// Spread flags of the pairs of a call: on the device, in the plan's scratch of
-// the mass reduction (both run on the plan's stream, and no pass comes between a
-// flag and its pair that reduces a mass).
-int64_t pair_flags(const sldg_plan_s* p) { return 4 * p->mass_nblocks; }
-int32_t* pair_flag(const sldg_plan_s* p, int i) {
-  return reinterpret_cast<int32_t*>(p->d_mass_part) + i;
-}
+// Spread flags of the pairs of a call: in the last entries of the plan's shift
+// table, past the call's tables (which leave room for them).
+constexpr int64_t kPairFlags = kMaxTableSet / 2;
+int32_t* pair_flag(const sldg_plan_s* p, int i) { return p->d_s + p->table_cap - 1 - i; }
 
 // The mean span of the shifts of 64 columns (largest less smallest, + 1) from
 // which a pair's sweeps run one by one: the fused pass then reads scattered rows.
@@ -1259,7 +1259,6 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
     int64_t nblocks = 0;
     ColPairArgs cp{};
     if (seq[q].dim > 0 && seq[q + 1].dim == seq[q].dim + 1 &&
-        pairs < pair_flags(p) &&
         colpair_eligible(p, seq[q].dim, seq[q].dep_mask, seq[q + 1].dep_mask, cp, nblocks)) {
       fused[(size_t)q] = 4;
       ++pairs;
@@ -1308,6 +1307,10 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
       tot += nt;
     }
     set.first[set.count] = tot;
+    if (pairs && tot + kPairFlags > p->table_cap) {
+      for (char& f : fused) f = f == 4 ? 0 : f;
+      pairs = 0;
+    }
     if (tot <= p->table_cap) {
       const hipError_t e = launch_line_tables_set(p->k, set, p->d_s, p->d_ab, p->stream);
       if (e != hipSuccess) return device_error(e, "line-table launch");
@@ -2098,7 +2101,8 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
       p->fuse && xy_eligible(p, dep[0], dep[1], m[0], hh[0], m[1], hh[1], &why);
   ColPairArgs cp{};
   int64_t nblocks = 0;
-  const bool vpair = tables && colpair_eligible(p, 2, dep[2], dep[3], cp, nblocks);
+  const bool vpair = tables && nx + 2 * nv + kPairFlags <= p->table_cap &&
+                     colpair_eligible(p, 2, dep[2], dep[3], cp, nblocks);
   auto x_sweeps = [&] {
     sldg_status st;
     if (pair) {
