@@ -168,7 +168,8 @@ typedef struct {
  * result is bitwise the same, but the pair then takes one pass instead of
  * two.  Other sweeps along 0, 1, 0 in a row (a Strang step X V X of an (x, v)
  * problem) run as one pass too, bitwise the three sweeps, where at most the
- * cell mean is FP64 and kernel timing (sldg_timing_enable) is off.  A sweep
+ * cell mean is FP64, kernel timing (sldg_timing_enable) is off and, on grids that
+ * fill the chip, the lines of dimension 0 are not short.  A sweep
  * along d >= 1 directly followed by one along d + 1, both with displacements of
  * the dimensions below d alone (v1 and v2 moved by E(x1, x2)), runs as one pass
  * too, bitwise the two, where at most the cell mean is FP64 and the dimensions
@@ -218,12 +219,14 @@ sldg_status sldg_split_steps_adjoint(sldg_plan_t plan, const sldg_sweep_desc* se
                                      int nsteps, double* mass0, void* hi0, double* mass1,
                                      void* hi1, int* result_buffer);
 
-/* Fusion of sweeps inside sldg_split_steps and sldg_split_steps_adjoint:
- * enable != 0 on (the default), 0 off (every sweep its own pass).  Off is the
- * faster choice where the displacements along the later dimension change by
- * more than about two cells over 64 neighbouring columns (fields far above one
- * cell a step, on coarse grids): X V X and pair passes then do the work of each
- * distinct shift, or read scattered rows.  Errors: SLDG_ERR_ARG. */
+/* Fusion of sweeps inside sldg_split_steps, sldg_split_steps_adjoint,
+ * sldg_vlasov_poisson_steps and sldg_vlasov_poisson_steps_2d2v: enable != 0 on (the
+ * default), 0 off (every sweep its own pass).  Passes take any displacements; pairs
+ * along d, d + 1 >= 1 whose shifts spread too far over neighbouring columns run as
+ * two sweeps by themselves, decided on the device.  Off can be the faster choice
+ * for X V X where the displacements along dimension 1 change by more than about a
+ * fifth of a cell from column to column (steep fields of many cells a step).
+ * Errors: SLDG_ERR_ARG. */
 sldg_status sldg_plan_set_fusion(sldg_plan_t plan, int enable);
 
 /*

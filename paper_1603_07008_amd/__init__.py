@@ -312,7 +312,8 @@ class Plan:
                                         _ptr(out_mass), _ptr(out_hi)), "sldg_advect_dims01")
 
     def set_fusion(self, enable):
-        """Fusion of (0, 1) sweep pairs in split_steps (sldg_plan_set_fusion)."""
+        """Fusion of sweeps in split steps, their transposes and the
+        Vlasov-Poisson steps (sldg_plan_set_fusion)."""
         _check(lib().sldg_plan_set_fusion(self.handle, 1 if enable else 0), "sldg_plan_set_fusion")
 
     def advect_dim_adjoint(self, dim, shift, dep_mask, in_mass, in_hi, out_mass, out_hi):

@@ -265,8 +265,8 @@ sldg_status build_sweep_impl(sldg_batch_s* b, int q) {
   return SLDG_OK;
 }
 
-// Rows per strip of the X V X pass.  A strip loads and X-sweeps three rows more
-// than it has; 8 rows but for the 16-bit tiers, whose waves are short, on batches of
+// Rows per strip of the X V X pass.  A strip loads four rows more than it has and
+// X-sweeps three more; 8 rows but for the 16-bit tiers, whose waves are short, on batches of
 // 16,384 strips of 16 on.  Measured (us a step with 4, 8, 16 rows): 512 problems of
 // 32-512 cells a side, 43,000 strips, FP32 991, 914, 937, BF16 824, 735, 711, FP64
 // 1548, 1431, 1449; 200 of them 443, 417, 426 and 374, 343, 343; 40 of them 121, 118,
