@@ -812,26 +812,32 @@ constexpr float pair_span(int k, sldg_tier tier) {
 constexpr int64_t kPairSmall = 10 << 20;
 bool pair_decides(const sldg_plan_s* p) { return p->lo_bytes + p->hi_bytes > kPairSmall; }
 
-// Flag i: whether the pair along d and d + 1 with its tables at entries pre1 and
-// pre2 is too spread.
-sldg_status decide_colpair(sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask2, int64_t pre1,
-                           int64_t pre2, int i) {
-  if (!pair_decides(p)) return SLDG_OK;
+// The decision of the pair along d and d + 1 with displacements shift1 and shift2,
+// at flag i (none for small states).
+PairSpread pair_decision(const sldg_plan_s* p, int d, const double* shift1, uint32_t mask1,
+                         const double* shift2, uint32_t mask2, int i) {
   PairSpread x{};
-  SweepArgs a1{}, a2{};
-  int64_t nt = 0;
-  describe(p, d, mask1, a1, nt);
-  describe(p, d + 1, mask2, a2, nt);
-  x.s1 = p->d_s + pre1;
-  x.s2 = p->d_s + pre2;
-  x.map1 = a1.map;
-  x.map2 = a2.map;
-  x.N1 = a1.N;
-  x.N2 = a2.N;
-  x.P = a1.P;
+  if (!pair_decides(p)) return x;
+  const double* const shift[2] = {shift1, shift2};
+  const uint32_t mask[2] = {mask1, mask2};
+  int64_t P = 1;
+  for (int e = 0; e < d; ++e) P *= p->n[e];
+  for (int w = 0; w < 2; ++w) {
+    int64_t run = 1, n = 1;
+    for (int e = 0; e < d; ++e) {
+      if (mask[w] >> e & 1) n *= p->n[e];
+      else if (n == 1) run *= p->n[e];
+    }
+    x.sigma[w] = shift[w];
+    x.run[w] = FastDiv::make((uint32_t)run);
+    x.n[w] = FastDiv::make((uint32_t)n);
+    x.N[w] = (double)p->n[d + w];
+    x.rN[w] = 1.0 / x.N[w];
+  }
+  x.P = (int32_t)P;
   x.most = pair_span(p->k, p->tier);
-  const hipError_t e = launch_pair_spread(x, pair_flag(p, i), p->stream);
-  return e == hipSuccess ? SLDG_OK : device_error(e, "pair decision launch");
+  x.flag = pair_flag(p, i);
+  return x;
 }
 
 // One of the pair's sweeps by itself, where the flag is set (in place where the
@@ -1282,6 +1288,7 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
   // plan's table storage together, each sweep computes its own (and X V X runs
   // sweep by sweep).
   std::vector<int64_t> pre((size_t)std::max(nseq, 1), -1);
+  std::vector<int> flag((size_t)std::max(nseq, 1), 0);
   if (nsteps > 0 && nseq > 0 && nseq <= kMaxTableSet) {
     TableSet set{};
     int64_t tot = 0;
@@ -1312,27 +1319,27 @@ static sldg_status run_steps(sldg_plan_t p, const sldg_sweep_desc* seq, int nseq
       pairs = 0;
     }
     if (tot <= p->table_cap) {
+      // pairs with the same tables share a flag; the first is decided beside the
+      // tables
+      for (int q = 0, i = 0; q + 1 < nseq; ++q) {
+        if (fused[(size_t)q] != 4) continue;
+        int f = -1;
+        for (int e = 0; e < q && f < 0; ++e)
+          if (fused[(size_t)e] == 4 && of[e] == of[q] && of[e + 1] == of[q + 1]) f = flag[(size_t)e];
+        if (f < 0) {
+          f = i++;
+          const PairSpread x = pair_decision(p, seq[q].dim, seq[q].shift, seq[q].dep_mask,
+                                             seq[q + 1].shift, seq[q + 1].dep_mask, f);
+          if (f == 0) set.pair = x;
+          const hipError_t e = f > 0 && x.flag ? launch_pair_spread(x, p->stream) : hipSuccess;
+          if (e != hipSuccess) return device_error(e, "pair decision launch");
+        }
+        flag[(size_t)q] = f;
+      }
       const hipError_t e = launch_line_tables_set(p->k, set, p->d_s, p->d_ab, p->stream);
       if (e != hipSuccess) return device_error(e, "line-table launch");
       for (int q = 0; q < nseq; ++q) pre[(size_t)q] = set.first[of[q]];
     }
-  }
-  std::vector<int> flag((size_t)std::max(nseq, 1), 0);
-  for (int q = 0, i = 0; q + 1 < nseq; ++q) {
-    if (fused[(size_t)q] != 4 || pre[(size_t)q] < 0) continue;
-    // pairs with the same tables share a flag
-    int f = -1;
-    for (int e = 0; e < q && f < 0; ++e)
-      if (fused[(size_t)e] == 4 && pre[(size_t)e] == pre[(size_t)q] &&
-          pre[(size_t)e + 1] == pre[(size_t)q + 1])
-        f = flag[(size_t)e];
-    if (f < 0) {
-      f = i++;
-      const sldg_status st = decide_colpair(p, seq[q].dim, seq[q].dep_mask, seq[q + 1].dep_mask,
-                                            pre[(size_t)q], pre[(size_t)q + 1], f);
-      if (st != SLDG_OK) return st;
-    }
-    flag[(size_t)q] = f;
   }
   int cur = 0;
   if (pre[0] >= 0 && (int64_t)nseq * nsteps > 1 && line_steps_eligible(p)) {
@@ -2072,6 +2079,10 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
     if (overlap(shift_x1, 8 * p->n[2], v, ob) || overlap(shift_x2, 8 * p->n[3], v, ob))
       tables = false;
   int64_t pre[4] = {-1, -1, -1, -1};
+  ColPairArgs cp{};
+  int64_t nblocks = 0;
+  const bool vpair = tables && nx + 2 * nv + kPairFlags <= p->table_cap &&
+                     colpair_eligible(p, 2, dep[2], dep[3], cp, nblocks);
   auto compute = [&](int d0, int64_t at) -> sldg_status {
     TableSet set{};
     set.count = 2;
@@ -2082,6 +2093,7 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
       set.sigma[i] = sh[d0 + i];
       pre[d0 + i] = at + set.first[i];
     }
+    if (d0 == 2 && vpair) set.pair = pair_decision(p, 2, sh[2], dep[2], sh[3], dep[3], 0);
     const hipError_t e =
         launch_line_tables_set(p->k, set, p->d_s + at, p->d_ab + 2 * o2 * at, p->stream);
     return e == hipSuccess ? SLDG_OK : device_error(e, "line-table launch");
@@ -2099,10 +2111,6 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
   const char* why = nullptr;
   const bool pair =
       p->fuse && xy_eligible(p, dep[0], dep[1], m[0], hh[0], m[1], hh[1], &why);
-  ColPairArgs cp{};
-  int64_t nblocks = 0;
-  const bool vpair = tables && nx + 2 * nv + kPairFlags <= p->table_cap &&
-                     colpair_eligible(p, 2, dep[2], dep[3], cp, nblocks);
   auto x_sweeps = [&] {
     sldg_status st;
     if (pair) {
@@ -2118,10 +2126,8 @@ sldg_status sldg_vlasov_poisson_steps_2d2v(sldg_plan_t p, int nsteps, const doub
   auto v_sweeps = [&](bool last) {
     sldg_status st;
     if (vpair && !(last && !result_buffer && nsteps % 2)) {
-      st = decide_colpair(p, 2, dep[2], dep[3], pre[2], pre[3], 0);
-      if (st == SLDG_OK)
-        st = run_colpair(p, 2, dep[2], dep[3], pre[2], pre[3], 0, m[cur], hh[cur], m[1 - cur],
-                         hh[1 - cur]);
+      st = run_colpair(p, 2, dep[2], dep[3], pre[2], pre[3], 0, m[cur], hh[cur], m[1 - cur],
+                       hh[1 - cur]);
       if (st == SLDG_OK) cur = 1 - cur;
     } else {
       st = sweep(2);

@@ -118,6 +118,22 @@ struct BatchItem {
   int32_t prob, kind, x, qg, z;
 };
 
+// Whether the columns' shifts of a pair of sweeps are spread (*flag): over the blocks
+// of 64 of the P columns (kPairSample of them, evenly spaced, where there are
+// more), whether the mean of the larger of the two sweeps' spans (largest less
+// smallest shift, modulo the extent, + 1) exceeds `most`.  Column c has entry
+// (c / run) mod n of a sweep's displacements: the line map's where the dimensions
+// it names follow one another, near it elsewhere.
+constexpr int32_t kPairSample = 32;
+struct PairSpread {
+  const double* sigma[2];
+  FastDiv run[2], n[2];
+  double N[2], rN[2];        // extents, and their reciprocals
+  int32_t P;
+  float most;
+  int32_t* flag;
+};
+
 // The line tables of up to kMaxTableSet sweeps computed in one launch
 // (component-major unless entry_major says otherwise): sweep q has first[q + 1] - first[q]
 // entries, period[q] cells along its dimension and displacements sigma[q].
@@ -129,6 +145,7 @@ struct TableSet {
   const double* sigma[kMaxTableSet];
   uint32_t entry_major;      // bit q: sweep q's table entry-major
   uint32_t adjoint;          // bit q: the transposed sweep's table
+  PairSpread pair;           // decided beside the tables (flag null: none)
 };
 
 // Launchers (defined in sldg_kernels.hip).  All return hipGetLastError().
@@ -204,18 +221,7 @@ hipError_t launch_colsweep(int k, int tier, const ColSweepArgs& a, int32_t nbloc
 template <int K, int TIER>
 hipError_t launch_colsweep_inst(const ColSweepArgs& a, int32_t nblocks, int32_t lds,
                                 hipStream_t st);
-// *flag = whether the columns' shifts of a pair are spread: over the blocks of 64
-// of the P columns (at most kPairSample of them, evenly spaced), the mean of the
-// larger of the two sweeps' spans (largest less smallest shift, modulo the
-// extent, + 1) exceeds `most`.
-constexpr int32_t kPairSample = 512;
-struct PairSpread {
-  const int32_t *s1, *s2;
-  LineMap map1, map2;
-  int32_t N1, N2, P;
-  float most;
-};
-hipError_t launch_pair_spread(const PairSpread& a, int32_t* flag, hipStream_t st);
+hipError_t launch_pair_spread(const PairSpread& a, hipStream_t st);
 // Sweeps of a 1D problem in one launch (sldg_line.h): one workgroup of `cells`
 // (1, 2, 4) cells a lane, lds bytes of LDS.
 struct LineStepsArgs;

@@ -150,6 +150,47 @@ __global__ __launch_bounds__(256) void line_tables_kernel(int64_t n, int64_t per
   line_table_component<K, ADJ>((int)blockIdx.y, sigma[t], period, s_out + t, ab_out + t * ts, cs);
 }
 
+// The span of the shifts floor(sg) of a wave modulo N: largest less smallest, + 1
+// (a displacement that is not finite has shift 0, as in the tables).
+__device__ __forceinline__ float wave_span(double sg, double N, double rN) {
+  const double f = isfinite(sg) ? floor(sg) : 0.0;
+  const uint64_t b = __builtin_bit_cast(uint64_t, f);
+  const uint64_t b0 = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32 |
+                      (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+  const double d = f - __builtin_bit_cast(double, b0);
+  const float r = (float)(d - N * rint(d * rN));   // of at most N / 2
+  return wave_max(r) + wave_max(-r) + 1.0f;
+}
+
+// By one workgroup of four waves: each takes a quarter of the sampled column
+// blocks, all its displacements loaded at once.
+__device__ void pair_spread(const PairSpread& a) {
+  __shared__ float sh[4];
+  constexpr int kRun = kPairSample / 4;
+  const int32_t lane = (int32_t)(threadIdx.x & 63), wave = (int32_t)(threadIdx.x >> 6);
+  const int32_t nblk = (a.P + 63) / 64, n = min(nblk, kPairSample);
+  const float step = (float)nblk / (float)n;
+  double sg[2][kRun];
+#pragma unroll
+  for (int i = 0; i < kRun; ++i) {
+    const int32_t blk = min((int32_t)((float)(wave + 4 * i) * step), nblk - 1);
+    const uint32_t col = (uint32_t)min(blk * 64 + lane, a.P - 1);
+#pragma unroll
+    for (int w = 0; w < 2; ++w) sg[w][i] = a.sigma[w][a.n[w].mod(a.run[w].div(col))];
+  }
+  float sum = 0.0f;
+#pragma unroll
+  for (int i = 0; i < kRun; ++i) {
+    const float span = fmaxf(wave_span(sg[0][i], a.N[0], a.rN[0]), wave_span(sg[1][i], a.N[1], a.rN[1]));
+    sum += wave + 4 * i < n ? span : 0.0f;
+  }
+  if (lane == 0) sh[wave] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) *a.flag = sh[0] + sh[1] + sh[2] + sh[3] > a.most * (float)n ? 1 : 0;
+}
+
+__global__ __launch_bounds__(256) void pair_spread_kernel(PairSpread a) { pair_spread(a); }
+
 // The tables of several sweeps in one launch: entry t of the flat range
 // belongs to sweep q with first[q] <= t < first[q + 1]; sweep q's table is the
 // one line_tables_kernel writes, at s_out + first[q] and
@@ -159,6 +200,10 @@ __global__ __launch_bounds__(256) void line_tables_set_kernel(TableSet set,
                                                               int32_t* __restrict__ s_out,
                                                               double* __restrict__ ab_out) {
   constexpr int64_t E = 2LL * (K + 1) * (K + 1);
+  if (set.pair.flag && blockIdx.x == gridDim.x - 1) {   // the block past the tables
+    if (blockIdx.y == 0) pair_spread(set.pair);
+    return;
+  }
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= set.first[set.count]) return;
   int q = 0;
@@ -219,7 +264,7 @@ hipError_t launch_line_tables_set(int k, const TableSet& set, int32_t* s_out, do
                                   hipStream_t st) {
   const int64_t n = set.first[set.count];
   if (n <= 0) return hipSuccess;
-  dim3 grid((unsigned)((n + 255) / 256), table_components(k)), block(256);
+  dim3 grid((unsigned)((n + 255) / 256 + (set.pair.flag ? 1 : 0)), table_components(k)), block(256);
   switch (k) {
     case 1: line_tables_set_kernel<1><<<grid, block, 0, st>>>(set, s_out, ab_out); break;
     case 2: line_tables_set_kernel<2><<<grid, block, 0, st>>>(set, s_out, ab_out); break;
@@ -458,42 +503,8 @@ hipError_t launch_colsweep(int k, int tier, const ColSweepArgs& a, int32_t nbloc
   return hipErrorInvalidValue;
 }
 
-// The span of a wave's shifts s (in [0, N)) modulo N: largest less smallest, + 1.
-__device__ __forceinline__ int32_t wave_span(int32_t s, int32_t N) {
-  int32_t d = s - __builtin_amdgcn_readfirstlane(s);
-  if (d > N / 2) d -= N;
-  if (d < -(N / 2)) d += N;
-  int32_t lo = d, hi = d;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    lo = min(lo, __shfl_xor(lo, o));
-    hi = max(hi, __shfl_xor(hi, o));
-  }
-  return hi - lo + 1;
-}
-
-// One workgroup: a wave per column block in turn.
-__global__ __launch_bounds__(1024) void pair_spread_kernel(PairSpread a, int32_t* flag) {
-  __shared__ int64_t sh[16];
-  const int32_t lane = (int32_t)(threadIdx.x & 63), wave = (int32_t)(threadIdx.x >> 6);
-  const int32_t nblk = (a.P + 63) / 64, n = min(nblk, kPairSample);
-  int64_t sum = 0;
-  for (int32_t i = wave; i < n; i += 16) {
-    const int32_t b = (int32_t)((int64_t)i * nblk / n);
-    const int32_t col = min(b * 64 + lane, a.P - 1);
-    sum += max(wave_span(a.s1[table_index(a.map1, col, 0)], a.N1),
-               wave_span(a.s2[table_index(a.map2, col, 0)], a.N2));
-  }
-  if (lane == 0) sh[wave] = sum;
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  sum = 0;
-  for (int w = 0; w < 16; ++w) sum += sh[w];
-  *flag = (double)sum > (double)a.most * n ? 1 : 0;
-}
-
-hipError_t launch_pair_spread(const PairSpread& a, int32_t* flag, hipStream_t st) {
-  pair_spread_kernel<<<1, 1024, 0, st>>>(a, flag);
+hipError_t launch_pair_spread(const PairSpread& a, hipStream_t st) {
+  pair_spread_kernel<<<1, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
