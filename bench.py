@@ -35,7 +35,7 @@ KERNEL_SOURCES = ["paper_1603_07008_amd/csrc/sldg_kernels.hip", "paper_1603_0700
                   "paper_1603_07008_amd/csrc/sldg_internal.h", "paper_1603_07008_amd/csrc/sldg_sweep.h",
                   "paper_1603_07008_amd/csrc/sldg_sweep_inst.hip", "paper_1603_07008_amd/csrc/sldg_fused.h",
                   "paper_1603_07008_amd/csrc/sldg_staged.h", "paper_1603_07008_amd/csrc/sldg_strang.h",
-                  "paper_1603_07008_amd/csrc/sldg_colpair.h"]
+                  "paper_1603_07008_amd/csrc/sldg_colpair.h", "paper_1603_07008_amd/csrc/sldg_colsweep.h"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_vlasov4d_48_k2.json")
 
 

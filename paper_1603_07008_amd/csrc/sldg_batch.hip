@@ -829,16 +829,17 @@ sldg_status sldg_batch_set_pass_tuning(sldg_batch_t b, int q, int rows) {
 }
 
 // Times the pass that starts at sweep q with each strip height (under an
-// allocation limit the rule's alone: other lists may not fit) and keeps the
-// fastest.
+// allocation limit the rule's alone: other lists may not fit), twice in turn (the
+// first launches of a run are slower), and keeps the fastest.
 static sldg_status tune_pass(sldg_batch_t b, int q, int reps, hipEvent_t e0, hipEvent_t e1) {
   static const int kRows[3] = {8, 16, 4};
   const int before = b->pass_rows[(size_t)q];
   int best_rows = before;
   double best = 1e300;
   sldg_status st = SLDG_OK;
-  for (int i = 0; i < (dev_alloc_limited() ? 1 : 3) && st == SLDG_OK; ++i) {
-    b->pass_rows[(size_t)q] = dev_alloc_limited() ? before : kRows[i];
+  const bool limited = dev_alloc_limited();
+  for (int i = 0; i < (limited ? 1 : 6) && st == SLDG_OK; ++i) {
+    b->pass_rows[(size_t)q] = limited ? before : kRows[i % 3];
     st = rebuild_pass(b, q);
     if (st == SLDG_OK) st = launch_pass(b, q, 0);             // warm-up
     (void)hipEventRecord(e0, b->stream);
