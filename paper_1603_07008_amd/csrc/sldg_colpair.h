@@ -44,10 +44,12 @@ struct ColPairArgs {
   int32_t P, N1, N2, Q;      // cells below d, extents of d and d + 1, cells above
   int32_t ms;                // o^d: mode-id stride of j_d (j_{d+1}: ms o)
   int32_t R, nstrip;         // rows of d + 1 per wave, strips
+  int32_t nrow;              // waves along d: ceil(N1 / L)
+  int32_t S, ngroup;         // strips whose waves fill whole workgroups, groups of S strips
   int32_t nblk;              // column blocks (64 columns) of a Q slab
-  int32_t nchunk;            // workgroups along d: ceil(N1 / (4 L))
+  int32_t nchunk;            // workgroups of a column block and group: ceil(nrow S / 4)
   float one;                 // 1.0f: the FP16 tier's unit scale
-  FastDiv fblk, fstrip, fchunk, fQ;
+  FastDiv fblk, fgroup, fchunk, fQ, frow;
   const int32_t* s1;         // the two sweeps' line tables, component-major
   const double* ab1;
   int64_t cs1;
@@ -252,7 +254,7 @@ __device__ __forceinline__ void colpair_body(const ColPairArgs& a, int32_t blk, 
     mats.fill(1, a.ab2, a.cs2, t2, lane, wave);
   }
   __syncthreads();
-  if (b1 >= N1 || (a.flag && *as_ctab(a.flag) != 0)) return;
+  if (strip >= a.nstrip || (a.flag && *as_ctab(a.flag) != 0)) return;
   // a sweep's matrices, read again at each use
   auto get = [&](int i, Mat<K, TIER>& M, Rows64<K, 1>& R64) {
     asm volatile("" ::: "memory");
@@ -414,18 +416,23 @@ template <int K, int TIER>
 __global__ __launch_bounds__(256, colpair_waves_per_simd(K, TIER)) void sweep_colpair_kernel(
     ColPairArgs a) {
   // tile order: the workgroups along d of a column block first (they share
-  // rows), then the column blocks, strips, slabs and groups
+  // rows), then the column blocks, groups of strips, slabs and spectator groups.
+  // The waves of a group of strips follow one another over the workgroups, so that
+  // none is idle where four do not divide those along d.
   const uint32_t w = blockIdx.x;
   const uint32_t q1 = a.fchunk.div(w);
   const int32_t cg = (int32_t)(w - q1 * (uint32_t)a.nchunk);
   const uint32_t q2 = a.fblk.div(q1);
   const int32_t blk = (int32_t)(q1 - q2 * (uint32_t)a.nblk);
-  const uint32_t q3 = a.fstrip.div(q2);
-  const int32_t strip = (int32_t)(q2 - q3 * (uint32_t)a.nstrip);
+  const uint32_t q3 = a.fgroup.div(q2);
+  const int32_t group = (int32_t)(q2 - q3 * (uint32_t)a.ngroup);
   const uint32_t g = a.fQ.div(q3);
   const int32_t slab = (int32_t)(q3 - g * (uint32_t)a.Q);
   const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
-  const int32_t chunk = cg * 4 + wave;
+  const uint32_t task = (uint32_t)(cg * 4 + wave);
+  const uint32_t of = a.frow.div(task);             // strip of the group (S: none)
+  const int32_t chunk = (int32_t)(task - of * (uint32_t)a.nrow);
+  const int32_t strip = of < (uint32_t)a.S ? group * a.S + (int32_t)of : a.nstrip;
   __shared__ PairMats<K, TIER> mats;
   if (g == 0 && a.n_lo == 1) colpair_body<K, TIER, 1>(a, blk, chunk, strip, slab, (int32_t)g, mats);
   else colpair_body<K, TIER, 0>(a, blk, chunk, strip, slab, (int32_t)g, mats);

@@ -733,10 +733,6 @@ sldg_status run_strang(sldg_plan_s* p, int post, const uint32_t (&mask)[3],
   return SLDG_OK;
 }
 
-// Workgroups below which a column pair takes shorter strips (16^4 cells, k = 2,
-// FP32: 23 us at 6 rows a strip, 33 us at 16).
-constexpr int64_t kPairBlocks = 512;
-
 // Whether the sweeps along d >= 1 and d + 1 can run as one pass
 // (sldg_colpair.h): displacements of the dimensions below d alone, at most the
 // cell mean FP64, a plane within 31-bit byte offsets and a launchable grid; and
@@ -747,7 +743,13 @@ constexpr int64_t kPairBlocks = 512;
 // columns x 64 x 4 rows 270 us against 316, x 2 rows 207 against 172).  For
 // k = 3 eight rows and seven eighths of the lanes: its waves hold one row of d
 // and read three (12^4 cells, 144 columns in 192 lanes, FP64: 50 us against 36;
-// 16^4 79 against 127).
+// 16^4 79 against 127).  Where the columns are no multiple of 16, the rows of a
+// wave straddle cache lines, and the two sweeps read them faster as long as they
+// find the state in the caches: from 16 to 128 MB a state the pair took 1.0 to 1.4
+// times the sweeps over random grids (2938 x 2 x 74, k = 3, bf16, 58 MB: 85 us
+// against 62; 37 x 99 x 10 x 7, k = 2, FP32, 82 against 62), below 0.5 to 0.7 (the
+// launches) and above, where the two buffers leave the 256 MB cache, 0.6 to 0.8;
+// aligned 0.8 in between.
 // Sets everything but the buffers and tables.
 bool colpair_eligible(const sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask2, ColPairArgs& x,
                       int64_t& nblocks) {
@@ -767,18 +769,37 @@ bool colpair_eligible(const sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask
   x.nblk = (int32_t)((P + 63) / 64);
   const bool high = p->k == 3;
   if (x.N1 < 2 || x.N2 < (high ? 8 : 4) || P * 8 < (high ? 7 : 6) * 64LL * x.nblk) return false;
+  const int64_t bytes = p->lo_bytes + p->hi_bytes;
+  if (P % 16 && bytes > (16 << 20) && bytes <= (128 << 20)) return false;
   const int32_t L = colpair_rows(p->k, (int)p->tier);
-  x.nchunk = (x.N1 + 4 * L - 1) / (4 * L);
-  nblocks = (int64_t)x.nchunk * x.nblk * x.Q * groups;
-  // Rows of d + 1 per wave (48^4: k = 2 FP32 728 us at 24, 749 at 48; bf16 448
-  // and 433; k = 1 FP32 154 and 165).
+  x.nrow = (x.N1 + L - 1) / L;
+  const int64_t tiles = (int64_t)x.nblk * x.Q * groups;
+  const int32_t whole = x.nrow % 4 == 0 ? 1 : x.nrow % 2 == 0 ? 2 : 4;
+  // Workgroups of strips of R rows.
+  auto workgroups = [&](int32_t R) {
+    x.R = R;
+    x.nstrip = (x.N2 + R - 1) / R;
+    x.S = std::min(whole, x.nstrip);
+    x.ngroup = (x.nstrip + x.S - 1) / x.S;
+    x.nchunk = (x.nrow * x.S + 3) / 4;
+    return tiles * x.ngroup * x.nchunk;
+  };
+  // Rows of d + 1 per wave: the fewest rounds of rows, three more than the strip has,
+  // over 256 compute units; a second workgroup on a unit takes 0.4 of the first's
+  // time more, and from there on the time grows with the workgroups.
   const int64_t most = p->k > 1 && (p->tier == SLDG_TIER_BF16 || p->tier == SLDG_TIER_FP16) ? 48 : 24;
-  const int64_t fill = x.N2 * nblocks / kPairBlocks;
-  const int64_t rows = std::min(most, std::max<int64_t>(fill, 6));
-  const int64_t ns = (x.N2 + rows - 1) / rows;
-  x.R = (int32_t)((x.N2 + ns - 1) / ns);
-  x.nstrip = (x.N2 + x.R - 1) / x.R;
-  nblocks *= x.nstrip;
+  double best = 1e300;
+  int32_t R = 0;
+  for (int64_t ns = (x.N2 + most - 1) / most; ns <= (x.N2 + 3) / 4; ++ns) {
+    const int32_t rows = (int32_t)((x.N2 + ns - 1) / ns);
+    const double u = (double)workgroups(rows) / 256.0;
+    const double cost = (rows + 3) * (u <= 1.0 ? 1.0 : std::max(1.4, 0.8 * u));
+    if (cost < best) {
+      best = cost;
+      R = rows;
+    }
+  }
+  nblocks = workgroups(R);
   // lines of both dimensions that the sweeps one by one hold in LDS
   ColSweepArgs line{};
   int64_t lds = 0;
@@ -902,7 +923,8 @@ sldg_status run_colpair(sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask2, i
   x.cells = p->cells;
   x.one = 1.0f;
   x.fblk = FastDiv::make((uint32_t)x.nblk);
-  x.fstrip = FastDiv::make((uint32_t)x.nstrip);
+  x.fgroup = FastDiv::make((uint32_t)x.ngroup);
+  x.frow = FastDiv::make((uint32_t)x.nrow);
   x.fchunk = FastDiv::make((uint32_t)x.nchunk);
   x.fQ = FastDiv::make((uint32_t)x.Q);
   x.flag = pair_decides(p) ? pair_flag(p, i) : nullptr;

@@ -42,7 +42,7 @@ def test_x_v_x(sl, tier, k, ns, amp):
 
 
 @pytest.mark.parametrize("tier,k", [("fp64", 2), ("fp32", 1), ("bf16", 2), ("fp16", 3)])
-@pytest.mark.parametrize("ns", [(60, 11, 13), (63, 150, 201), (300, 51, 59)])
+@pytest.mark.parametrize("ns", [(60, 11, 13), (112, 151, 101), (304, 51, 59)])
 @pytest.mark.parametrize("amp", [0.4, 1.5, 30.0])
 def test_column_pair(sl, tier, k, ns, amp):
     _guarded(sl, sl.Plan(ns, k, tier),

@@ -237,18 +237,20 @@ def test_pair_of_spread_shifts(sl, tier, k, amp):
     the fused pass (each lane its own rows) and in larger ones, which run the
     sweeps one by one through lines in LDS where the shifts are spread."""
     for ndouble in (0, 1):
-        for ns in ((60, 11, 13), (60, 170, 175 if k == 1 else 90)):
-            _pair_both(sl, ns, k, tier, 1, 1, [_uniform(60, amp, 1), _uniform(60, amp, 2)],
+        for ns in ((60, 11, 13), (48 if k < 3 else 64, 170, 175 if k == 1 else 90)):
+            _pair_both(sl, ns, k, tier, 1, 1, [_uniform(ns[0], amp, 1), _uniform(ns[0], amp, 2)],
                        ndouble=ndouble, nsteps=2)
 
 
 @pytest.mark.parametrize("ns,d,mask,k,tier,fused", [
-    ((300, 50, 59), 1, 1, 2, "bf16", True),            # 128 columns a tile, the last short
+    ((304, 50, 59), 1, 1, 2, "bf16", True),            # 128 columns a tile, the last short
+    ((300, 50, 59), 1, 1, 2, "bf16", False),           # rows across cache lines, in the caches
+    ((300, 5, 59), 1, 1, 2, "bf16", True), ((300, 170, 59), 1, 1, 2, "bf16", True),
     ((64, 3, 600), 1, 1, 3, "fp64", True),             # 8 columns a tile
     ((64, 3, 700), 1, 1, 3, "fp64", False),            # lines too long for LDS
-    ((64, 900, 8), 1, 1, 2, "fp32", True), ((63, 150, 200), 1, 1, 1, "fp16", True),
-    ((12, 9, 36, 47), 2, 3, 2, "fp32", True), ((60, 29, 36, 7), 1, 1, 2, "bf16", True),
-    ((60, 9, 26, 27), 2, 1, 1, "fp32", True), ((10, 5, 13, 14, 15), 2, 2, 2, "bf16", True)])
+    ((64, 900, 8), 1, 1, 2, "fp32", True), ((64, 150, 200), 1, 1, 1, "fp16", True),
+    ((16, 7, 36, 47), 2, 3, 2, "fp32", True), ((48, 29, 36, 7), 1, 1, 2, "bf16", True),
+    ((48, 9, 26, 27), 2, 1, 1, "fp32", True), ((16, 3, 13, 14, 15), 2, 2, 2, "bf16", True)])
 def test_lines_in_lds(sl, ns, d, mask, k, tier, fused):
     n = int(np.prod([ns[e] for e in range(len(ns)) if mask >> e & 1]))
     _pair_both(sl, ns, k, tier, d, mask, [_uniform(n, 50.0, 1), _uniform(n, 9.0, 2)], fused=fused)
@@ -294,8 +296,8 @@ def test_default_shapes_of_uneven_grids(sl, ns, k, tier, want):
 def test_transposed_pair(sl, tier, k, amp):
     """The transpose of the sweeps d + 1, d is a pair along d, d + 1."""
     import torch
-    ns = (60, 40, 90)
-    seq = [(2, 1, _uniform(60, amp, 3)), (1, 1, _uniform(60, amp, 4))]
+    ns = (64, 40, 90)
+    seq = [(2, 1, _uniform(64, amp, 3)), (1, 1, _uniform(64, amp, 4))]
     _adjoint_both(sl, ns, k, tier, seq, 2)
     plan = sl.Plan(ns, k, tier)
     a, b = plan.empty_state(), plan.empty_state()
@@ -306,4 +308,40 @@ def test_transposed_pair(sl, tier, k, amp):
     assert plan.timing_read(-2)[0] == 2
     plan.timing_enable(False)
     torch.cuda.synchronize()
+    plan.close()
+
+
+@pytest.mark.parametrize("n1", [2, 3, 5, 6, 8, 9, 11, 13])
+@pytest.mark.parametrize("n2", [4, 9, 23, 50])
+def test_waves_of_a_pair_over_workgroups(sl, n1, n2):
+    """The waves along d of one, two or four strips fill whole workgroups; the last
+    group has fewer strips."""
+    for k, tier in ((1, "fp16"), (2, "fp32"), (3, "bf16")):
+        _pair_both(sl, (62, n1, n2), k, tier, 1, 1, [_uniform(62, 0.4, 1), _uniform(62, 0.4, 2)],
+                   fused=k < 3 or n2 >= 8)
+        _pair_both(sl, (8, 8, n1, n2), k, tier, 2, 1, [_uniform(8, 0.4, 1), _uniform(8, 6.0, 2)],
+                   fused=k < 3 or n2 >= 8)
+
+
+@pytest.mark.parametrize("ns,k,tier", [
+    ((2938, 2, 74), 3, "bf16"), ((6995, 9, 33), 2, "bf16"), ((35, 11, 31, 48), 2, "bf16"),
+    ((37, 99, 10, 7), 2, "fp32"), ((59, 53, 13, 16), 2, "bf16"), ((2731, 2, 24), 2, "fp64"),
+    ((128, 100, 100), 2, "bf16"), ((626, 4, 116), 2, "fp64")])
+def test_pair_of_any_grid_costs_no_more_than_the_sweeps(sl, ns, k, tier):
+    """Displacements of less than half a cell: 0.7 to 1.0 of the sweeps, and with
+    workgroups of idle waves 1.3 to 1.8."""
+    import torch
+    plan = sl.Plan(ns, k, tier)
+    a, b = plan.empty_state(), plan.empty_state()
+    for t in (*a, *b):
+        t.zero_()
+    d = len(ns) - 2
+    n = int(np.prod(ns[:d]))
+    seq = [(d + i, (1 << d) - 1, torch.linspace(-0.4, 0.4, n, dtype=torch.float64, device="cuda"))
+           for i in range(2)]
+    t = []
+    for fuse in (False, True):
+        plan.set_fusion(fuse)
+        t.append(_time(plan, seq, 8, a, b))
+    assert t[1] <= 1.15 * t[0], t
     plan.close()
