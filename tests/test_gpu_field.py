@@ -124,3 +124,20 @@ def test_field_entry_points_reject_bad_arguments(sl):
     with pytest.raises(sl.SldgError) as ei:
         p2.poisson_shift(m, h, -1.0, 0.1, 0.1)
     assert ei.value.status == sl.SLDG_ERR_ARG
+
+
+@pytest.mark.parametrize("nv", [1, 2, 7, 8, 9, 16, 17, 64, 121, 128, 129, 520])
+def test_field_of_any_number_of_v_rows(sl, nv):
+    """Chunks of one row to more than the workgroup's waves, the last ones short
+    or empty."""
+    import torch
+    for nx, k, tier in ((70, 1, "fp64"), (64, 3, "fp32"), (5, 2, "bf16")):
+        st = O.to_tier(inputs.random_coefficients(2, k, nx * nv, seed=nv), tier, 1, k, 2)
+        plan = sl.Plan((nx, nv), k, tier)
+        m, h = upload_nd(st, plan)
+        field = torch.empty(nx, dtype=torch.float64, device="cuda")
+        plan.poisson_shift(m, h, 0.37, 0.21, 0.1, field_out=field)
+        want = O.poisson_field(st, (nx, nv), k, 0.37, 0.21)
+        scale = float(np.max(np.abs(want)))
+        assert np.max(np.abs(field.cpu().numpy() - want)) <= 1e-12 * scale, (nx, k, tier)
+        plan.close()
