@@ -784,9 +784,13 @@ bool colpair_eligible(const sldg_plan_s* p, int d, uint32_t mask1, uint32_t mask
     x.nchunk = (x.nrow * x.S + 3) / 4;
     return tiles * x.ngroup * x.nchunk;
   };
-  // Rows of d + 1 per wave: the fewest rounds of rows, three more than the strip has,
-  // over 256 compute units; a second workgroup on a unit takes 0.4 of the first's
-  // time more, and from there on the time grows with the workgroups.
+  // Rows of d + 1 per wave: the least time, taken as the rows of a wave (R + 2, and
+  // the tables for about one) times the rounds of workgroups on 256 compute units.  A
+  // second workgroup on a unit takes 0.4 of the first's time more, and from there on
+  // the time grows with the workgroups (fits of 699 random grids: 1.3 to 1.7 times the
+  // first for two, 0.8 to 1.1 for each of many).  16^4, k = 2, FP32: 6 rows 25 us, 16
+  // rows 33; 48^4: FP32 24 rows 727 us, 48 rows 749, bf16 448 and 433, k = 1 154 and
+  // 165, hence the most rows.
   const int64_t most = p->k > 1 && (p->tier == SLDG_TIER_BF16 || p->tier == SLDG_TIER_FP16) ? 48 : 24;
   double best = 1e300;
   int32_t R = 0;
